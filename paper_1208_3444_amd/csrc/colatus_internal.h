@@ -84,11 +84,14 @@ __device__ __forceinline__ void two_sum_add(float &hi, float &lo, float v)
 //   y1 = y0 + (y0 / 2) (1 - s y0^2),
 // which squares the error (measured maximum 4e-15 relative over 2^-60..2^20).
 // Every FP64 kernel that must reproduce another's r^-1 bit for bit uses this.
-__device__ __forceinline__ double rsqrt_refined(double s)
+__device__ __forceinline__ double rsqrt_refine(double s, double y0)
 {
-    const double y0 = __builtin_amdgcn_rsq(s);
     const double e = fma(-s * y0, y0, 1.0);
     return fma(0.5 * y0, e, y0);
+}
+__device__ __forceinline__ double rsqrt_refined(double s)
+{
+    return rsqrt_refine(s, __builtin_amdgcn_rsq(s));
 }
 
 // External terms added to the comoving sum g of every particle, each with

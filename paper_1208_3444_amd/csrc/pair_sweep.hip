@@ -50,14 +50,21 @@ template <> struct V4<double> { using type = double4; };
 __device__ __forceinline__ float rsqrt_t(float s) { return __builtin_amdgcn_rsqf(s); }
 __device__ __forceinline__ double rsqrt_t(double s) { return rsqrt_refined(s); }
 
+// The hardware estimate of s^{-1/2} alone, and the weights made from it: the
+// pair loops issue the estimates of several pairs back to back and finish
+// them afterwards (see sym_chunk).
+__device__ __forceinline__ float rsq_raw(float s) { return __builtin_amdgcn_rsqf(s); }
+__device__ __forceinline__ double rsq_raw(double s) { return __builtin_amdgcn_rsq(s); }
+__device__ __forceinline__ float rsqrt_from(float, float y) { return y; }
+__device__ __forceinline__ double rsqrt_from(double s, double y) { return rsqrt_refine(s, y); }
+
 // s^{-3/2} for FP64 pairs that do not need s^{-1/2} itself: with
 // y = v_rsq_f64(s) (relative error below 6e-8) and e = 1 - s y^2,
 // s^{-3/2} = y^3 (1 - e)^{-3/2} = y^3 (1 + 3e/2 + O(e^2)).  The first-order
 // correction applied to y^3 leaves about (15/8) e^2 < 3e-14 relative, one
-// operation fewer than refining y (rsqrt_refined) and cubing it.
-__device__ __forceinline__ double rinv3_fp64(double s)
+// operation fewer than refining y (rsqrt_refine) and cubing it.
+__device__ __forceinline__ double rinv3_from(double s, double y)
 {
-    const double y = __builtin_amdgcn_rsq(s);
     const double y2 = y * y;
     const double e = fma(-s, y2, 1.0);
     const double y3 = y2 * y;
@@ -66,6 +73,27 @@ __device__ __forceinline__ double rinv3_fp64(double s)
 
 __device__ __forceinline__ float fma_t(float a, float b, float c) { return fmaf(a, b, c); }
 __device__ __forceinline__ double fma_t(double a, double b, double c) { return fma(a, b, c); }
+
+// Phase marks of the pair loops.  Gfx950 issues two VALU instructions of two
+// waves of a SIMD together (one each, 2.1 cycles per instruction) as long as
+// both are in ordinary FP32 arithmetic; a v_rsq_f32 (8 cycles) or a DPP move of
+// one wave stops the other's pairing, and spread over the loop they undo it:
+// measured on registers alone, 56 FMAs with 4 v_rsq and 6 DPP moves take 265
+// cycles, and 173 when the v_rsq and moves are issued back to back at a raised
+// wave priority (s_setprio), which lets one wave finish its burst while the
+// others wait at theirs and then run their FMAs side by side.  burst_begin /
+// burst_end bracket such a run; neither lets the compiler move code across.
+__device__ __forceinline__ void phase_mark() { __builtin_amdgcn_sched_barrier(0); }
+__device__ __forceinline__ void burst_begin()
+{
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(1);
+}
+__device__ __forceinline__ void burst_end()
+{
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(0);
+}
 
 
 // Centre of the bounding box of the block's valid targets, for every thread.
@@ -376,6 +404,21 @@ __device__ __forceinline__ double wave_rotate(double v)
     return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
+// lane l receives the value lane (l + 1) mod 64 held (DPP wave_rol:1).
+__device__ __forceinline__ float wave_rotate_back(float v)
+{
+    return __builtin_bit_cast(
+        float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x134, 0xF, 0xF, true));
+}
+__device__ __forceinline__ double wave_rotate_back(double v)
+{
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)u, 0x134, 0xF, 0xF, true);
+    const uint32_t hi =
+        (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), 0x134, 0xF, 0xF, true);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
 // Far-away coordinate of a missing target or source of the symmetric loops.
 // Forward: s overflows (FP32) or r^-3 underflows (FP64) and the pair adds 0.
 // Adjoint: s must stay finite so that d.u does (r^-3 underflows to 0).
@@ -389,53 +432,63 @@ template <> __device__ __forceinline__ double adj_pad<double>() { return 1e150; 
 // 64 steps of one source chunk against the lane's R targets.  REACT: also
 // accumulate the reaction on the travelling source (q*); EQM: the box's common
 // mass leaves the loop (weights r^-3 and r^-1 only).
+//
+// A step is three phases: the R separations, a burst of the R reciprocal
+// square roots with the rotations of everything that travels, and the
+// weights with the accumulations (see burst_begin for why).  The positions
+// rotate for the next step; the masses and reactions rotate just before this
+// step uses them (the masses start one lane back, the reactions, zero at
+// first, take one more rotation at the end), so that all rotations share the
+// one burst.  A piece of a diagonal (R = 1, no reaction) takes U = 4 steps at
+// a time for the same batch of four.  The order of every sum is that of the
+// plain loop.  Measured (FP32, equal masses, one 64^3 evaluation / 20 steps
+// at 32^3): 13.0 / 4.66 ms with the compiler's own order, 10.3 / 3.63 ms so.
 template <typename T, int R, bool REACT, bool EQM, bool PHI, bool MASK>
 __device__ __forceinline__ void sym_chunk(T sx, T sy, T sz, T sm, T &qx, T &qy, T &qz, T &qp,
                                           const T (&xi)[R], const T (&yi)[R], const T (&zi)[R],
                                           const T (&mi)[R], T eps2, T (&ax)[R], T (&ay)[R],
                                           T (&az)[R], T (&ap)[R])
 {
-#pragma unroll 2
-    for (int k = 0; k < 64; ++k) {
+    constexpr int U = R == 1 && !REACT ? 4 : 1;
+    constexpr int B = U * R;
+    static_assert(U == 1 || !REACT, "a reaction rotates every step");
+    if constexpr (!EQM)
+        sm = wave_rotate_back(sm);
+#pragma unroll 1
+    for (int k = 0; k < 64; k += U) {
+        T dx[B], dy[B], dz[B], s[B], y[B], su[U];
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const T dx = sx - xi[r];
-            const T dy = sy - yi[r];
-            const T dz = sz - zi[r];
-            T s = fma_t(dx, dx, eps2);
-            s = fma_t(dy, dy, s);
-            s = fma_t(dz, dz, s);
-            T rinv, w;
-            if constexpr (sizeof(T) == 8 && !PHI) {
-                w = rinv3_fp64(s);
-                if constexpr (MASK)
-                    w = s > (T)0.0 ? w : (T)0.0;
-            } else {
-                rinv = rsqrt_t(s);
-                if constexpr (MASK)
-                    rinv = s > (T)0.0 ? rinv : (T)0.0;
-                w = rinv * (rinv * rinv);
+        for (int u = 0; u < U; ++u) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int b = u * R + r;
+                dx[b] = sx - xi[r];
+                dy[b] = sy - yi[r];
+                dz[b] = sz - zi[r];
+                s[b] = fma_t(dx[b], dx[b], eps2);
+                s[b] = fma_t(dy[b], dy[b], s[b]);
+                s[b] = fma_t(dz[b], dz[b], s[b]);
             }
-            const T wt = EQM ? w : sm * w;
-            ax[r] = fma_t(wt, dx, ax[r]);
-            ay[r] = fma_t(wt, dy, ay[r]);
-            az[r] = fma_t(wt, dz, az[r]);
-            if constexpr (PHI)
-                ap[r] += EQM ? rinv : sm * rinv;
-            if constexpr (REACT) {
-                const T ws = EQM ? w : mi[r] * w;
-                qx = fma_t(-ws, dx, qx);
-                qy = fma_t(-ws, dy, qy);
-                qz = fma_t(-ws, dz, qz);
-                if constexpr (PHI)
-                    qp += EQM ? rinv : mi[r] * rinv;
+            if (u + 1 < U) {
+                sx = wave_rotate(sx);
+                sy = wave_rotate(sy);
+                sz = wave_rotate(sz);
             }
         }
+        burst_begin();
+#pragma unroll
+        for (int b = 0; b < B; ++b)
+            y[b] = rsq_raw(s[b]);
+        phase_mark();
         sx = wave_rotate(sx);
         sy = wave_rotate(sy);
         sz = wave_rotate(sz);
-        if constexpr (!EQM)
-            sm = wave_rotate(sm);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if constexpr (!EQM)
+                sm = wave_rotate(sm);
+            su[u] = sm;
+        }
         if constexpr (REACT) {
             qx = wave_rotate(qx);
             qy = wave_rotate(qy);
@@ -443,6 +496,49 @@ __device__ __forceinline__ void sym_chunk(T sx, T sy, T sz, T sm, T &qx, T &qy, 
             if constexpr (PHI)
                 qp = wave_rotate(qp);
         }
+        burst_end();
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int b = u * R + r;
+                T rinv, w;
+                if constexpr (sizeof(T) == 8 && !PHI) {
+                    w = rinv3_from(s[b], y[b]);
+                    if constexpr (MASK)
+                        w = s[b] > (T)0.0 ? w : (T)0.0;
+                } else {
+                    rinv = rsqrt_from(s[b], y[b]);
+                    if constexpr (MASK)
+                        rinv = s[b] > (T)0.0 ? rinv : (T)0.0;
+                    w = rinv * (rinv * rinv);
+                }
+                const T wt = EQM ? w : su[u] * w;
+                ax[r] = fma_t(wt, dx[b], ax[r]);
+                ay[r] = fma_t(wt, dy[b], ay[r]);
+                az[r] = fma_t(wt, dz[b], az[r]);
+                if constexpr (PHI)
+                    ap[r] += EQM ? rinv : su[u] * rinv;
+                if constexpr (REACT) {
+                    // -(pull) accumulates with the opposite sign until the end:
+                    // the same roundings, and no negated operand
+                    const T ws = EQM ? w : mi[r] * w;
+                    qx = fma_t(ws, dx[b], qx);
+                    qy = fma_t(ws, dy[b], qy);
+                    qz = fma_t(ws, dz[b], qz);
+                    if constexpr (PHI)
+                        qp += EQM ? rinv : mi[r] * rinv;
+                }
+            }
+        }
+        phase_mark();
+    }
+    if constexpr (REACT) {
+        qx = -wave_rotate(qx);
+        qy = -wave_rotate(qy);
+        qz = -wave_rotate(qz);
+        if constexpr (PHI)
+            qp = wave_rotate(qp);
     }
 }
 
@@ -659,12 +755,11 @@ __device__ __forceinline__ void sym_item(const WorkItem &w, const double *__rest
     }
 }
 
-// One wave per workgroup with four targets per lane is held to 80 VGPRs so
-// that six waves share each SIMD (measured 10 % faster than four at 32^3;
-// two 8-byte values of the item loop spill, outside the pair loop).
+// One wave per workgroup with four targets per lane is held to 96 VGPRs so
+// that five waves share each SIMD.
 template <typename T, int ACC, int R, int W, bool PHI, bool MASK>
 __global__ __launch_bounds__(64 * W)
-__attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && R * W == 4 ? 6 : 1))) void
+__attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && R * W == 4 ? 5 : 1))) void
 pair_sweep_sym_kernel(
     const double *__restrict__ x, const double *__restrict__ m, int64_t N,
     const WorkItem *__restrict__ items, int n_items, int *__restrict__ counter,
@@ -845,7 +940,7 @@ __device__ __forceinline__ void grp_item(const WorkItem &w, const double *__rest
 
 template <typename T, bool PHI, bool MASK>
 __global__ __launch_bounds__(64 * kGroupWaves)
-__attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 6 : 3))) void
+__attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 5 : 3))) void
 pair_sweep_sym_grp_kernel(
     const double *__restrict__ x, const double *__restrict__ m, int64_t N,
     const WorkItem *__restrict__ items, int n_groups, int *__restrict__ counter,
