@@ -24,7 +24,9 @@ struct WorkItem {
     int32_t slice;    // partial-sum slot of the targets
     int32_t box;
     int32_t rslice;   // partial-sum slot of the sources' reaction (form 2)
-    int16_t kind;     // form 2: 0 = pair of parts, 1 = piece of a diagonal,
+    int16_t kind;     // form 2: 0 = pair of parts, 1 = 64 targets against a part
+                      // (a piece of a diagonal, or one side of a pair), 2 = 64
+                      // sources' reaction from a part (the other side),
                       // -1 = padding of a group (grouped form)
     int8_t tmate;     // grouped form: 1 if the targets' partial sums are added
                       // to those of wave (this wave ^ 1) of the group
@@ -121,9 +123,12 @@ struct TileCfg {
     int tpb;      // threads per block (= sources per LDS tile in forms 0, 1)
     int slices;   // source slices per box (form 2: parts of R * tpb particles)
     int form;     // FP32 pair-loop form (see launch_pair_sweep); 0 for FP64
-    int group = 0; // form 2 with R = 4, tpb = 64: 2x2 groups of part pairs
-                   // per workgroup of four waves (pair_sweep_sym_grp_kernel)
+    int group = 0; // form 2 with R = 4, tpb = 64: 1 = 2x2 groups of part pairs
+                   // per workgroup of four waves (pair_sweep_sym_grp_kernel),
+                   // kOneSided = both sides of a pair as items of their own
+                   // (the periodic real space of small boxes, FP32 pairs)
 };
+constexpr int kOneSided = 2;
 
 // How the readers add the slots a sweep of this shape writes (SlotMode).
 // The symmetric form with FP32 pairs and parts of at most 256 particles

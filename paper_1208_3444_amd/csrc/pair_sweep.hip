@@ -91,6 +91,13 @@ __device__ __forceinline__ float in_vgpr(float c)
     return c;
 }
 __device__ __forceinline__ double in_vgpr(double c) { return c; }
+// c ? v : other with v computed in every lane (a select, never a branch
+// around v's computation).
+__device__ __forceinline__ float select_value(bool c, float v, float other)
+{
+    asm volatile("" : "+v"(v));
+    return c ? v : other;
+}
 __device__ __forceinline__ void phase_mark() { __builtin_amdgcn_sched_barrier(0); }
 __device__ __forceinline__ void burst_begin()
 {
@@ -2048,8 +2055,12 @@ __device__ __forceinline__ uint32_t wave_rotate_u(uint32_t v)
 {
     return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x13C, 0xF, 0xF, true);
 }
+__device__ __forceinline__ uint32_t wave_rotate_back_u(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x134, 0xF, 0xF, true);
+}
 
-// One FP32 pair.  With u = alpha r, Hastings' approximation (Abramowitz and
+// FP32 pairs.  With u = alpha r, Hastings' approximation (Abramowitz and
 // Stegun 7.1.26; absolute error at most 1.5e-7, a few FP32 units of the
 // kernel it enters) gives erf(u) = 1 - t p(t) g, t = 1 / (1 + 0.3275911 u),
 // g = exp(-u^2), p of fourth degree, so that
@@ -2058,27 +2069,67 @@ __device__ __forceinline__ uint32_t wave_rotate_u(uint32_t v)
 // but raises the exponent's rounding error sixfold.)  At r = 0 the pair's
 // terms are selected (w = 0, psi = phi_self), not branched to, so that the
 // target rows interleave.
-template <bool PHI>
-__device__ __forceinline__ void ewald_pair_fx(float dx, float dy, float dz, const EwaldFx &E,
-                                              float &w, float &psi)
+//
+// 64 steps of one source chunk, in the phases of sym_chunk: separations; a
+// burst of the two square roots and the exponential of every pair; the
+// argument of t; a burst of the reciprocals with the rotations; weights and
+// accumulations.  The polynomial's constants sit in vector registers
+// (in_vgpr).  A piece of a diagonal (R = 1) takes four steps at a time.
+struct EwaldFxRegs {
+    float eps2, c_exp, c_t, c_g, one, k4, k3, k2, k1, k0;
+};
+
+__device__ __forceinline__ EwaldFxRegs ewald_fx_regs(const EwaldFx &E)
 {
-    const float r2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-    const float rs = __builtin_amdgcn_rsqf(r2 + E.eps2);
-    const float ri = __builtin_amdgcn_rsqf(r2);  // +inf at r = 0: not selected
-    const float r = r2 * ri;
-    const float g = __builtin_amdgcn_exp2f(E.c_exp * r2);
-    const float t = __builtin_amdgcn_rcpf(fmaf(E.c_t, r, 1.0f));
-    const float p =
-        fmaf(t, fmaf(t, fmaf(t, fmaf(t, 1.061405429f, -1.453152027f), 1.421413741f),
-                     -0.284496736f),
-             0.254829592f);
-    const float P = fmaf(-g, fmaf(t, p, E.c_g * r), 1.0f);
-    const bool nz = r2 > 0.0f;
-    w = nz ? fmaf(-P, ri * (ri * ri), rs * (rs * rs)) : 0.0f;
-    if constexpr (PHI) {
-        const float erf_u = fmaf(-t * p, g, 1.0f);
-        psi = nz ? fmaf(-erf_u, ri, rs) : E.phi_self;
+    return {in_vgpr(E.eps2),       in_vgpr(E.c_exp),       in_vgpr(E.c_t),
+            in_vgpr(E.c_g),        in_vgpr(1.0f),          in_vgpr(1.061405429f),
+            in_vgpr(-1.453152027f), in_vgpr(1.421413741f), in_vgpr(-0.284496736f),
+            in_vgpr(0.254829592f)};
+}
+
+// r^2, the burst of square roots and exponentials, and the argument of t, of
+// B pairs with separations (dx, dy, dz).
+template <int B>
+__device__ __forceinline__ void ewald_fx_roots(const EwaldFxRegs &C, const float (&dx)[B],
+                                               const float (&dy)[B], const float (&dz)[B],
+                                               float (&r2)[B], float (&rs)[B], float (&ri)[B],
+                                               float (&r)[B], float (&g)[B], float (&t)[B])
+{
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+        r2[b] = fmaf(dx[b], dx[b], fmaf(dy[b], dy[b], dz[b] * dz[b]));
+        rs[b] = r2[b] + C.eps2;
+        g[b] = C.c_exp * r2[b];
     }
+    burst_begin();
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+        rs[b] = __builtin_amdgcn_rsqf(rs[b]);
+        ri[b] = __builtin_amdgcn_rsqf(r2[b]);  // +inf at r = 0: not selected
+        g[b] = __builtin_amdgcn_exp2f(g[b]);
+    }
+    burst_end();
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+        r[b] = r2[b] * ri[b];
+        t[b] = fmaf(C.c_t, r[b], C.one);
+    }
+}
+
+// w (and psi) of one pair from its roots, t = 1 / (1 + 0.3275911 u).
+template <bool PHI>
+__device__ __forceinline__ float ewald_fx_weight(const EwaldFxRegs &C, float phi_self, float r2,
+                                                 float rs, float ri, float r, float g, float t,
+                                                 float &psi)
+{
+    const float p = fmaf(t, fmaf(t, fmaf(t, fmaf(t, C.k4, C.k3), C.k2), C.k1), C.k0);
+    const float P = fmaf(-g, fmaf(t, p, C.c_g * r), C.one);
+    const bool nz = r2 > 0.0f;
+    if constexpr (PHI) {
+        const float erf_u = fmaf(-t * p, g, C.one);
+        psi = select_value(nz, fmaf(-erf_u, ri, rs), phi_self);
+    }
+    return select_value(nz, fmaf(-P, ri * (ri * ri), rs * (rs * rs)), 0.0f);
 }
 
 template <int R, bool REACT, bool PHI>
@@ -2089,33 +2140,42 @@ __device__ __forceinline__ void ewald_chunk_fx(uint32_t sx, uint32_t sy, uint32_
                                                const EwaldFx &E, float (&ax)[R], float (&ay)[R],
                                                float (&az)[R], float (&ap)[R])
 {
-    for (int k = 0; k < 64; ++k) {
+    constexpr int U = R == 1 && !REACT ? 4 : 1;
+    constexpr int B = U * R;
+    const EwaldFxRegs C = ewald_fx_regs(E);
+    sm = wave_rotate_back(sm);
+#pragma unroll 1
+    for (int k = 0; k < 64; k += U) {
+        float dx[B], dy[B], dz[B], r2[B], rs[B], ri[B], r[B], g[B], t[B], su[U];
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const float dx = (float)(int32_t)(sx - xi[r]);
-            const float dy = (float)(int32_t)(sy - yi[r]);
-            const float dz = (float)(int32_t)(sz - zi[r]);
-            float w, psi;
-            ewald_pair_fx<PHI>(dx, dy, dz, E, w, psi);
-            const float wt = sm * w;
-            ax[r] = fmaf(wt, dx, ax[r]);
-            ay[r] = fmaf(wt, dy, ay[r]);
-            az[r] = fmaf(wt, dz, az[r]);
-            if constexpr (PHI)
-                ap[r] = fmaf(sm, psi, ap[r]);
-            if constexpr (REACT) {
-                const float ws = mi[r] * w;
-                qx = fmaf(-ws, dx, qx);
-                qy = fmaf(-ws, dy, qy);
-                qz = fmaf(-ws, dz, qz);
-                if constexpr (PHI)
-                    qp = fmaf(mi[r], psi, qp);
+        for (int u = 0; u < U; ++u) {
+#pragma unroll
+            for (int q = 0; q < R; ++q) {
+                const int b = u * R + q;
+                dx[b] = (float)(int32_t)(sx - xi[q]);
+                dy[b] = (float)(int32_t)(sy - yi[q]);
+                dz[b] = (float)(int32_t)(sz - zi[q]);
+            }
+            if (u + 1 < U) {
+                sx = wave_rotate_u(sx);
+                sy = wave_rotate_u(sy);
+                sz = wave_rotate_u(sz);
             }
         }
+        ewald_fx_roots<B>(C, dx, dy, dz, r2, rs, ri, r, g, t);
+        burst_begin();
+#pragma unroll
+        for (int b = 0; b < B; ++b)
+            t[b] = __builtin_amdgcn_rcpf(t[b]);
+        phase_mark();
         sx = wave_rotate_u(sx);
         sy = wave_rotate_u(sy);
         sz = wave_rotate_u(sz);
-        sm = wave_rotate(sm);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            sm = wave_rotate(sm);
+            su[u] = sm;
+        }
         if constexpr (REACT) {
             qx = wave_rotate(qx);
             qy = wave_rotate(qy);
@@ -2123,7 +2183,134 @@ __device__ __forceinline__ void ewald_chunk_fx(uint32_t sx, uint32_t sy, uint32_
             if constexpr (PHI)
                 qp = wave_rotate(qp);
         }
+        burst_end();
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+#pragma unroll
+            for (int q = 0; q < R; ++q) {
+                const int b = u * R + q;
+                float psi = 0.0f;
+                const float w = ewald_fx_weight<PHI>(C, E.phi_self, r2[b], rs[b], ri[b], r[b],
+                                                     g[b], t[b], psi);
+                const float wt = su[u] * w;
+                ax[q] = fmaf(wt, dx[b], ax[q]);
+                ay[q] = fmaf(wt, dy[b], ay[q]);
+                az[q] = fmaf(wt, dz[b], az[q]);
+                if constexpr (PHI)
+                    ap[q] = fmaf(su[u], psi, ap[q]);
+                if constexpr (REACT) {
+                    // the opposite sign until the end, as in sym_chunk
+                    const float ws = mi[q] * w;
+                    qx = fmaf(ws, dx[b], qx);
+                    qy = fmaf(ws, dy[b], qy);
+                    qz = fmaf(ws, dz[b], qz);
+                    if constexpr (PHI)
+                        qp = fmaf(mi[q], psi, qp);
+                }
+            }
+        }
+        phase_mark();
     }
+    if constexpr (REACT) {
+        qx = -wave_rotate(qx);
+        qy = -wave_rotate(qy);
+        qz = -wave_rotate(qz);
+        if constexpr (PHI)
+            qp = wave_rotate(qp);
+    }
+}
+
+// A reaction piece (kind 2, FP32 pairs): the reactions of 64 sources, one per
+// lane, from a part's targets, four per lane, which travel the other way
+// around the wave.  A source meets the targets in the order in which a
+// travelling source of a pair item does, so its sum has the same bits.
+template <bool PHI>
+__device__ __forceinline__ void ewald_react_fx(const WorkItem &w, const double *__restrict__ X,
+                                               const double *__restrict__ Y,
+                                               const double *__restrict__ Z,
+                                               const double *__restrict__ m, int64_t N,
+                                               double *__restrict__ part,
+                                               double *__restrict__ part_phi, const double sc,
+                                               const EwaldFx &E)
+{
+    const int lane = threadIdx.x & 63;
+    const EwaldFxRegs C = ewald_fx_regs(E);
+    const int64_t j = w.j0 + lane;
+    const bool jv = j < w.j1;
+    const uint32_t sx = jv ? fx_coord(X[j], sc) : 0u, sy = jv ? fx_coord(Y[j], sc) : 0u,
+                   sz = jv ? fx_coord(Z[j], sc) : 0u;
+    uint32_t xi[4], yi[4], zi[4];
+    float mi[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int64_t i = w.i0 + (int64_t)(r * 64 + lane);
+        const bool v = i < w.i1;
+        xi[r] = v ? fx_coord(X[i], sc) : 0u;
+        yi[r] = v ? fx_coord(Y[i], sc) : 0u;
+        zi[r] = v ? fx_coord(Z[i], sc) : 0u;
+        // one lane ahead: the masses rotate just before their use
+        mi[r] = wave_rotate(v ? (float)m[i] : 0.0f);
+    }
+    float qx = 0.0f, qy = 0.0f, qz = 0.0f, qp = 0.0f;
+#pragma unroll 1
+    for (int k = 0; k < 64; ++k) {
+        float dx[4], dy[4], dz[4], r2[4], rs[4], ri[4], r[4], g[4], t[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            dx[q] = (float)(int32_t)(sx - xi[q]);
+            dy[q] = (float)(int32_t)(sy - yi[q]);
+            dz[q] = (float)(int32_t)(sz - zi[q]);
+        }
+        ewald_fx_roots<4>(C, dx, dy, dz, r2, rs, ri, r, g, t);
+        burst_begin();
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            t[q] = __builtin_amdgcn_rcpf(t[q]);
+        phase_mark();
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            xi[q] = wave_rotate_back_u(xi[q]);
+            yi[q] = wave_rotate_back_u(yi[q]);
+            zi[q] = wave_rotate_back_u(zi[q]);
+            mi[q] = wave_rotate_back(mi[q]);
+        }
+        burst_end();
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            float psi = 0.0f;
+            const float wq = ewald_fx_weight<PHI>(C, E.phi_self, r2[q], rs[q], ri[q], r[q], g[q],
+                                                  t[q], psi);
+            const float ws = mi[q] * wq;
+            qx = fmaf(ws, dx[q], qx);
+            qy = fmaf(ws, dy[q], qy);
+            qz = fmaf(ws, dz[q], qz);
+            if constexpr (PHI)
+                qp = fmaf(mi[q], psi, qp);
+        }
+        phase_mark();
+    }
+    if (!jv)
+        return;
+    const double sf = sc * sc;
+    const int64_t rs = (int64_t)w.rslice;
+    float *pf = reinterpret_cast<float *>(part);
+    pf[(rs * 3 + 0) * N + j] = (float)(sf * (double)-qx);
+    pf[(rs * 3 + 1) * N + j] = (float)(sf * (double)-qy);
+    pf[(rs * 3 + 2) * N + j] = (float)(sf * (double)-qz);
+    if constexpr (PHI)
+        reinterpret_cast<float *>(part_phi)[rs * N + j] = (float)(sc * (double)qp);
+}
+
+__device__ __forceinline__ EwaldFx ewald_fx(double eps2, double sc, double alpha)
+{
+    const double a_fx = alpha / sc;  // alpha in fixed-point units
+    EwaldFx E;
+    E.eps2 = (float)(eps2 * sc * sc);
+    E.c_exp = (float)(-a_fx * a_fx * 1.4426950408889634);
+    E.c_t = (float)(0.3275911 * a_fx);
+    E.c_g = (float)(1.1283791670955126 * a_fx);
+    E.phi_self = E.eps2 > 0.0f ? __builtin_amdgcn_rsqf(E.eps2) : 0.0f;
+    return E;
 }
 
 template <int R, bool REACT, bool PHI>
@@ -2132,18 +2319,10 @@ __device__ __forceinline__ void ewald_item_fx(const WorkItem &w, const double *_
                                               const double *__restrict__ Z,
                                               const double *__restrict__ m, int64_t N,
                                               double *__restrict__ part,
-                                              double *__restrict__ part_phi, const double L,
-                                              const double alpha)
+                                              double *__restrict__ part_phi, const double sc,
+                                              const EwaldFx &E)
 {
     const int lane = threadIdx.x & 63;
-    const double sc = 4294967296.0 / L;  // fixed-point units per length
-    const double a_fx = alpha / sc;      // alpha in those units
-    EwaldFx E;
-    E.eps2 = (float)(w.eps2 * sc * sc);
-    E.c_exp = (float)(-a_fx * a_fx * 1.4426950408889634);
-    E.c_t = (float)(0.3275911 * a_fx);
-    E.c_g = (float)(1.1283791670955126 * a_fx);
-    E.phi_self = E.eps2 > 0.0f ? __builtin_amdgcn_rsqf(E.eps2) : 0.0f;
     const double sf = sc * sc;  // force sums back to lengths
     uint32_t xi[R], yi[R], zi[R];
     float mi[R], ax[R], ay[R], az[R], ap[R];
@@ -2219,10 +2398,14 @@ __global__ __launch_bounds__(64) void ewald_real_kernel(
         return;
     const WorkItem w = items[it];
     if constexpr (sizeof(T) == 4) {
+        const double sc = 4294967296.0 / L;  // fixed-point units per length
+        const EwaldFx E = ewald_fx(w.eps2, sc, alpha);
         if (w.kind == 0)
-            ewald_item_fx<4, true, PHI>(w, X, Y, Z, m, N, part, part_phi, L, alpha);
+            ewald_item_fx<4, true, PHI>(w, X, Y, Z, m, N, part, part_phi, sc, E);
+        else if (w.kind == 1)
+            ewald_item_fx<1, false, PHI>(w, X, Y, Z, m, N, part, part_phi, sc, E);
         else
-            ewald_item_fx<1, false, PHI>(w, X, Y, Z, m, N, part, part_phi, L, alpha);
+            ewald_react_fx<PHI>(w, X, Y, Z, m, N, part, part_phi, sc, E);
     } else {
         EwaldReal<T> E;
         E.L = (T)L;
