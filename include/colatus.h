@@ -293,9 +293,11 @@ int colatus_run_he(double *x, double *v, const double *m, int64_t N, double eps,
  * Plummer correction, reciprocal part exp(-q^2/4 alpha^2)/q^2 cos(q . d),
  * constant -pi / (alpha^2 L^3)) and Psi_self the particle's own images and
  * background (-2.8372974794806 / L for one particle: the simple cubic
- * Madelung constant).  The library takes alpha and the cutoffs so that the
- * neglected real-space images and reciprocal terms fall below 1e-15 (FP64)
- * or 3e-9 (FP32 forms) of the kernel: real space on the nearest image only
+ * Madelung constant).  The library takes the splitting and its cutoffs so
+ * that the neglected real-space images and reciprocal terms fall below 1e-15
+ * (FP64; the split is by a prolate spheroidal window in place of the
+ * Gaussian, the same sum) or 3e-9 (FP32 forms) of the kernel: real space on
+ * the nearest image only
  * (the pair sweep's symmetric loop, in the given precision; FP32 pairs
  * take coordinates rounded to multiples of L / 2^32 and the nearest image
  * of those, an exact tie along an axis giving -L/2), reciprocal

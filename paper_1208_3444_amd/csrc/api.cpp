@@ -4,6 +4,7 @@
 // colatus_step, colatus_run, colatus_adjoint and colatus_force_vjp.
 #include "colatus.h"
 #include "colatus_internal.h"
+#include "ewald_window.h"
 
 #include <hip/hip_runtime.h>
 #include <rocprofiler-sdk-roctx/roctx.h>
@@ -209,9 +210,9 @@ struct Workspace {
         box_mass, att_acc, he_x, track_idx, track_slot, twiddle, ftle_idx;
     // periodic boundaries: the reciprocal-space plan (vectors and weights for
     // one box side and precision) and its work buffers
-    Buffer ew_segs, ew_segs_sk, ew_coef, ew_skp, ew_S, ew_kpg, ew_kpp, ew_msum, ew_g, ew_p;
-    double ew_L = 0.0, ew_alpha = 0.0;
-    int ew_nmax = -1, ew_nsegs = 0, ew_K = 0;
+    Buffer ew_plan, ew_poly, ew_tiles, ew_range, ew_dest, ew_table, ew_skp, ew_kp, ew_msum, ew_g, ew_p;
+    double ew_L = 0.0, ew_alpha = 0.0, ew_self = 0.0, ew_bg = 0.0;
+    int ew_kind = -1, ew_units = 0, ew_slots_p = 0;
     // work lists by (N, boxes, softenings, tile shape); fwd / adj: the lists
     // selected by the current call's forward and adjoint set-up
     std::vector<WorkList *> lists;
@@ -228,7 +229,7 @@ struct Workspace {
         return {&part,     &part_phi,   &coef,  &p,        &diag_part,  &diag_out,
                 &counters, &lam_x,      &lam_p, &ckpt,     &seg,        &box_mass,
                 &att_acc,  &he_x,       &track_idx, &track_slot, &twiddle, &ftle_idx,
-                &ew_segs,  &ew_segs_sk, &ew_coef, &ew_skp, &ew_S, &ew_kpg, &ew_kpp, &ew_msum,
+                &ew_plan,  &ew_poly, &ew_tiles, &ew_range, &ew_dest, &ew_table, &ew_skp, &ew_kp, &ew_msum,
                 &ew_g,     &ew_p};
     }
 };
@@ -1440,17 +1441,17 @@ namespace {
 // ---------------------------------------------------------------------------
 // Periodic boundaries (Ewald summation).
 // ---------------------------------------------------------------------------
-// The Ewald kernel's real-space part C(u) = erfc(u) + (2u/sqrt(pi)) e^{-u^2}
-// (u = alpha r) and the reciprocal weights exp(-pi^2 n^2 / (alpha L)^2)
-// both fall below the precision's resolution tol: alpha from C(alpha L / 2)
-// = tol (the nearest image is the only real-space term kept; the others lie
-// at least L / 2 away), n_max from the weight at tol.
-constexpr double kEwaldTolFP64 = 1e-15;
+// FP32 pairs split the sum by a Gaussian: the kernel's real-space part
+// C(u) = erfc(u) + (2u/sqrt(pi)) e^{-u^2} (u = alpha r) and the reciprocal
+// weights exp(-pi^2 n^2 / (alpha L)^2) both fall below tol: alpha from
+// C(alpha L / 2) = tol (the nearest image is the only real-space term kept;
+// the others lie at least L / 2 away), n_max from the weight at tol.  FP64
+// pairs split it by the prolate window (ewald_window.h; n_max = kWindowN).
 constexpr double kEwaldTolFP32 = 3e-9;
 
-void ewald_parameters(double L, int precision, double &alpha, int &nmax)
+void ewald_parameters(double L, double &alpha, int &nmax)
 {
-    const double tol = precision == COLATUS_FP64 ? kEwaldTolFP64 : kEwaldTolFP32;
+    const double tol = kEwaldTolFP32;
     auto C = [](double u) { return std::erfc(u) + 1.1283791670955126 * u * std::exp(-u * u); };
     double lo = 0.0, hi = 12.0;
     for (int it = 0; it < 200; ++it) {
@@ -1461,93 +1462,202 @@ void ewald_parameters(double L, int precision, double &alpha, int &nmax)
             hi = mid;
     }
     alpha = 2.0 * hi / L;
-    nmax = (int)std::ceil(alpha * L / M_PI * std::sqrt(std::log(1.0 / tol)));
+    nmax = (int)std::ceil(2.0 * hi / M_PI * std::sqrt(std::log(1.0 / tol)));
 }
 
-// The half-space reciprocal vectors n != 0, |n| <= nmax (n_x > 0, or n_x = 0
-// and n_y > 0, or n_x = n_y = 0 and n_z > 0), as column segments of up to
-// kEwaldSegLen consecutive n_z, with their weights 2 (4 pi / L^3)
-// exp(-k^2 / 4 alpha^2) / k^2; uploaded once per (L, precision).  A second
-// copy of the segments, longest first, feeds the structure-factor kernel,
-// whose lanes each take a segment: a wave of equal counts runs its loop over
-// the k without idle lanes (its sums are stored by k, so the order changes
-// no result).
-int ensure_ewald_plan(Workspace *ws, double L, int precision, hipStream_t s)
+// The reciprocal-space plan of a box side and a splitting (kind 0: window,
+// 1: Gaussian): columns, structure-factor tiles, the table's layout, and the
+// field kernel's tile ranges of equal work for 1, 2, 4, ... 2^kEwMaxRangeLog
+// ranges.  Host only.
+constexpr int kEwMaxRangeLog = 5;
+
+struct EwaldPlanHost {
+    EwaldSkPlan sk{};
+    std::vector<EwaldColTile> tiles;
+    std::vector<int32_t> range;
+    std::vector<EwaldDest> dest;
+    std::vector<double> poly;  // kind 0: the real-space polynomials in this box's units
+    int slots_p = 0, n_units = 0;
+    int64_t table_len = 0;
+    double alpha = 0.0, self_c = 0.0, bg_c = 0.0;
+};
+
+int ewald_plan(double L, int kind, EwaldPlanHost &P)
 {
-    double alpha = 0.0;
-    int nmax = 0;
-    ewald_parameters(L, precision, alpha, nmax);
-    if (ws->ew_L == L && ws->ew_alpha == alpha && ws->ew_nmax == nmax)
-        return COLATUS_OK;
-    ws->ew_nmax = -1;
-    std::vector<EwaldSeg> segs;
-    std::vector<double> coef;
-    const double vol = L * L * L;
+    int nmax = kWindowN;
+    if (kind == 0) {
+        const EwaldWindow &w = ewald_window();
+        const double rc = 0.5 * L;
+        P.self_c = -w.self / rc;
+        P.bg_c = -2.0 * M_PI * w.mean_s2 * rc * rc / (L * L * L);
+        for (double f : w.force)
+            P.poly.push_back(f / (rc * rc * rc));
+        for (double f : w.pot)
+            P.poly.push_back(f / rc);
+    } else {
+        ewald_parameters(L, P.alpha, nmax);
+        P.self_c = -2.0 * P.alpha / std::sqrt(M_PI);
+        P.bg_c = -M_PI / (P.alpha * P.alpha * L * L * L);
+    }
+    if (nmax < 1 || nmax > kEwMaxN)
+        return COLATUS_EINVAL;
+    // weight of one reciprocal vector
+    std::vector<double> wk((size_t)nmax * nmax + 1, 0.0);
+    for (int n2 = 1; n2 <= nmax * nmax; ++n2) {
+        const double k2 = 4.0 * M_PI * M_PI * n2 / (L * L);
+        const double window =
+            kind == 0 ? ewald_window().weight(n2) : std::exp(-k2 / (4.0 * P.alpha * P.alpha));
+        wk[(size_t)n2] = 4.0 * M_PI / (L * L * L) * window / k2;
+    }
+    struct Col {
+        int nx, ny, zm;
+    };
+    std::vector<Col> cols;
     for (int nx = 0; nx <= nmax; ++nx)
-        for (int ny = -nmax; ny <= nmax; ++ny) {
+        for (int ny = nx == 0 ? 0 : -nmax; ny <= nmax; ++ny) {
             const int r2 = nx * nx + ny * ny;
             if (r2 > nmax * nmax)
                 continue;
-            const int zm = (int)std::floor(std::sqrt((double)(nmax * nmax - r2)));
-            int z0 = -zm;
-            if (nx == 0 && ny < 0)
-                continue;
-            if (nx == 0 && ny == 0)
-                z0 = 1;
-            for (int zb = z0; zb <= zm; zb += kEwaldSegLen) {
-                EwaldSeg g;
-                g.nx = nx;
-                g.ny = ny;
-                g.z0 = zb;
-                g.cnt = std::min(kEwaldSegLen, zm - zb + 1);
-                g.k0 = (int)coef.size();
-                for (int q = 0; q < g.cnt; ++q) {
-                    const double kx = 2.0 * M_PI * nx / L, ky = 2.0 * M_PI * ny / L,
-                                 kz = 2.0 * M_PI * (zb + q) / L;
-                    const double k2 = kx * kx + ky * ky + kz * kz;
-                    coef.push_back(2.0 * 4.0 * M_PI / vol * std::exp(-k2 / (4.0 * alpha * alpha)) /
-                                   k2);
-                }
-                segs.push_back(g);
+            int zm = 0;
+            while (r2 + (zm + 1) * (zm + 1) <= nmax * nmax)
+                ++zm;
+            cols.push_back({nx, ny, zm});
+        }
+    // longest columns first: row tiles of eight, the field's column tiles of four
+    std::stable_sort(cols.begin(), cols.end(),
+                     [](const Col &a, const Col &b) { return a.zm > b.zm; });
+    const int C = (int)cols.size();
+    const int tiles = (C + 7) / 8;
+    int pairs = 0;
+    while (pairs < tiles && cols[(size_t)pairs * 8].zm >= 8)
+        ++pairs;
+    if (tiles > kEwMaxTiles || pairs > 8 * kEwPairs || tiles - pairs > 8 * kEwSingles)
+        return COLATUS_EINVAL;
+    P.sk.n_pairs = pairs;
+    P.slots_p = (pairs + 7) / 8;
+    for (auto &w : P.sk.slots)
+        for (int16_t &s : w)
+            s = -1;
+    // pairs to the waves in turn, the singles first to those with a pair less
+    for (int t = 0; t < pairs; ++t)
+        P.sk.slots[t % 8][t / 8] = (int16_t)t;
+    int next = pairs;
+    for (int s = 0; s < kEwSingles; ++s)
+        for (int k = 7; k >= 0 && next < tiles; --k)
+            P.sk.slots[k][kEwPairs + s] = (int16_t)next++;
+    P.n_units = tiles + pairs;
+    for (int c = 0; c < tiles * 8; ++c)
+        P.sk.cols[c] = c < C ? make_int2(cols[(size_t)c].nx, cols[(size_t)c].ny) : make_int2(0, 0);
+    std::vector<int64_t> cost(1, 0);
+    for (int c0 = 0; c0 < C; c0 += 4) {
+        EwaldColTile t{};
+        t.ks = cols[(size_t)c0].zm / 2 + 1;
+        for (int k = 0; k < 4; ++k) {
+            // a missing column repeats (0, 0) with a zero table
+            t.nx[k] = c0 + k < C ? cols[(size_t)(c0 + k)].nx : 0;
+            t.ny[k] = c0 + k < C ? cols[(size_t)(c0 + k)].ny : 0;
+        }
+        P.tiles.push_back(t);
+        cost.push_back(cost.back() + 4 * t.ks + 6);  // in 32 cycles: 2 products, the epilogue
+    }
+    P.table_len = (int64_t)P.tiles.size() * (kEwQ / 2) * 64;
+    P.dest.assign((size_t)P.n_units * 256, EwaldDest{-1, -1, 0.0, 0.0});
+    for (int t = 0; t < tiles; ++t)
+        for (int qt = 0; qt < (t < pairs ? 2 : 1); ++qt) {
+            const int u = t < pairs ? 2 * t + qt : t + pairs;
+            for (int e = 0; e < 256; ++e) {
+                const int v = e / 64, lane = e % 64;
+                const int row = lane / 16 + 4 * v, colm = lane % 16;
+                const int c = t * 8 + row / 2, q = qt * 8 + colm / 2;
+                if (c >= C || q > cols[(size_t)c].zm)
+                    continue;
+                const Col &col = cols[(size_t)c];
+                const int n2 = col.nx * col.nx + col.ny * col.ny + q * q;
+                // k and -k: twice the vector's weight; +q and -q: twice again;
+                // the column (0, 0) holds both of a pair k, -k itself
+                const double twice = (q > 0 ? 2.0 : 1.0) * (col.nx == 0 && col.ny == 0 ? 1.0 : 2.0);
+                const double wt = twice * wk[(size_t)n2];
+                // element (A_r or A_i, B_c or B_s): a, b, c, d.  Place of (q, trig,
+                // output): step q / 2 of the tile, lane 16 (2 (q % 2) + trig) + 4 column
+                // + output (V_r, V_i, V'_r, V'_i)
+                const int part = row & 1, trig = colm & 1;
+                auto place = [&](int tr, int output) {
+                    return (c / 4 * (kEwQ / 2) + q / 2) * 64 + 16 * (2 * (q % 2) + tr) +
+                           4 * (c % 4) + output;
+                };
+                EwaldDest d;
+                d.v = place(trig, part);  // a, b in V_r; c, d in V_i; cos with B_c, sin with B_s
+                // V'_r = q (c B_s - d B_c), V'_i = q (b B_c - a B_s)
+                d.z = place(1 - trig, part ? 2 : 3);
+                d.wv = wt;
+                d.wz = (part == trig ? -1.0 : 1.0) * q * wt;
+                P.dest[(size_t)u * 256 + e] = d;
             }
         }
-    std::vector<EwaldSeg> segs_sk = segs;
-    std::stable_sort(segs_sk.begin(), segs_sk.end(),
-                     [](const EwaldSeg &a, const EwaldSeg &b) { return a.cnt > b.cnt; });
+    for (int lg = 0; lg <= kEwMaxRangeLog; ++lg) {
+        const int n = 1 << lg;
+        for (int r = 0; r <= n; ++r)
+            P.range.push_back((int32_t)(std::lower_bound(cost.begin(), cost.end(),
+                                                         cost.back() * r / n) -
+                                        cost.begin()));
+    }
+    return COLATUS_OK;
+}
+
+int upload(Buffer &b, const void *src, size_t bytes, hipStream_t s)
+{
+    CHECK_RC(ensure(b, bytes));
+    if (bytes == 0)
+        return COLATUS_OK;
+    CHECK_HIP(hipMemcpyAsync(b.ptr, src, bytes, hipMemcpyHostToDevice, s));
+    return COLATUS_OK;
+}
+
+// The workspace's plan for (L, splitting of the precision).
+int ensure_ewald_plan(Workspace *ws, double L, int precision, hipStream_t s)
+{
+    const int kind = precision == COLATUS_FP64 ? 0 : 1;
+    if (ws->ew_L == L && ws->ew_kind == kind)
+        return COLATUS_OK;
+    ws->ew_kind = -1;
+    EwaldPlanHost P;
+    CHECK_RC(ewald_plan(L, kind, P));
     // the previous plan's buffers may still be read by queued work
     CHECK_HIP(hipStreamSynchronize(s));
-    CHECK_RC(ensure(ws->ew_segs, std::max<size_t>(1, segs.size()) * sizeof(EwaldSeg)));
-    CHECK_RC(ensure(ws->ew_segs_sk, std::max<size_t>(1, segs.size()) * sizeof(EwaldSeg)));
-    CHECK_RC(ensure(ws->ew_coef, std::max<size_t>(1, coef.size()) * sizeof(double)));
-    if (!segs.empty()) {
-        CHECK_HIP(hipMemcpyAsync(ws->ew_segs.ptr, segs.data(), segs.size() * sizeof(EwaldSeg),
-                                 hipMemcpyHostToDevice, s));
-        CHECK_HIP(hipMemcpyAsync(ws->ew_segs_sk.ptr, segs_sk.data(),
-                                 segs_sk.size() * sizeof(EwaldSeg), hipMemcpyHostToDevice, s));
-        CHECK_HIP(hipMemcpyAsync(ws->ew_coef.ptr, coef.data(), coef.size() * sizeof(double),
-                                 hipMemcpyHostToDevice, s));
-        CHECK_HIP(hipStreamSynchronize(s));  // the host tables are local
-    }
+    CHECK_RC(upload(ws->ew_plan, &P.sk, sizeof P.sk, s));
+    CHECK_RC(upload(ws->ew_poly, P.poly.data(), P.poly.size() * sizeof(double), s));
+    CHECK_RC(upload(ws->ew_tiles, P.tiles.data(), P.tiles.size() * sizeof(EwaldColTile), s));
+    CHECK_RC(upload(ws->ew_range, P.range.data(), P.range.size() * sizeof(int32_t), s));
+    CHECK_RC(upload(ws->ew_dest, P.dest.data(), P.dest.size() * sizeof(EwaldDest), s));
+    CHECK_RC(ensure(ws->ew_table, (size_t)P.table_len * sizeof(double)));
+    CHECK_HIP(launch_fill(static_cast<double *>(ws->ew_table.ptr), P.table_len, 0.0, s));
+    CHECK_HIP(hipStreamSynchronize(s));  // the host tables are local
     ws->ew_L = L;
-    ws->ew_alpha = alpha;
-    ws->ew_nsegs = (int)segs.size();
-    ws->ew_K = (int)coef.size();
-    ws->ew_nmax = nmax;
+    ws->ew_alpha = P.alpha;
+    ws->ew_self = P.self_c;
+    ws->ew_bg = P.bg_c;
+    ws->ew_units = P.n_units;
+    ws->ew_slots_p = P.slots_p;
+    ws->ew_kind = kind;
     return COLATUS_OK;
 }
 
 // Work buffers of the reciprocal-space sums for N particles, and the
 // launch arguments.
-int ewald_args(Workspace *ws, const double *x, const double *m, int64_t N, EwaldArgs &A)
+int ewald_args(Workspace *ws, const double *x, const double *m, int64_t N, bool want_p,
+               EwaldArgs &A)
 {
-    const int n_sk = (int)std::max<int64_t>(1, std::min<int64_t>(256, N / 256));
-    const int64_t blocks = (N + 63) / 64;
-    const int n_kc = (int)std::max<int64_t>(1, std::min<int64_t>(64, (8192 + blocks - 1) / blocks));
-    const size_t K = (size_t)std::max(1, ws->ew_K);
-    CHECK_RC(ensure(ws->ew_skp, (size_t)n_sk * K * 2 * sizeof(double)));
-    CHECK_RC(ensure(ws->ew_S, K * 2 * sizeof(double)));
-    CHECK_RC(ensure(ws->ew_kpg, (size_t)n_kc * 3 * (size_t)N * sizeof(double)));
-    CHECK_RC(ensure(ws->ew_kpp, (size_t)n_kc * (size_t)N * sizeof(double)));
+    // structure factors: a block per CU, chunks of whole tiles of 32 particles
+    const int64_t chunk = std::max<int64_t>(1, (N + 256 * 32 - 1) / (256 * 32)) * 32;
+    const int n_sk = (int)((N + chunk - 1) / chunk);
+    // the field: ranges of columns for about 512 blocks of 128 particles
+    const int64_t blocks = (N + 127) / 128;
+    int lg = 0;
+    while (lg < kEwMaxRangeLog && (blocks << lg) < 512)
+        ++lg;
+    const int n_ranges = 1 << lg;
+    CHECK_RC(ensure(ws->ew_skp, (size_t)n_sk * ws->ew_units * 256 * sizeof(double)));
+    CHECK_RC(ensure(ws->ew_kp, (size_t)n_ranges * 4 * (size_t)N * sizeof(double)));
     CHECK_RC(ensure(ws->ew_msum, sizeof(double)));
     CHECK_RC(ensure(ws->ew_g, 3 * (size_t)N * sizeof(double)));
     CHECK_RC(ensure(ws->ew_p, (size_t)N * sizeof(double)));
@@ -1555,35 +1665,41 @@ int ewald_args(Workspace *ws, const double *x, const double *m, int64_t N, Ewald
     A.m = m;
     A.N = N;
     A.L = ws->ew_L;
-    A.alpha = ws->ew_alpha;
-    A.segs = static_cast<const EwaldSeg *>(ws->ew_segs.ptr);
-    A.segs_sk = static_cast<const EwaldSeg *>(ws->ew_segs_sk.ptr);
-    A.n_segs = ws->ew_nsegs;
-    A.K = ws->ew_K;
-    A.coef = static_cast<const double *>(ws->ew_coef.ptr);
-    A.sk_part = static_cast<double2 *>(ws->ew_skp.ptr);
+    A.sk_plan = static_cast<const EwaldSkPlan *>(ws->ew_plan.ptr);
+    A.n_units = ws->ew_units;
+    A.sk_slots_p = ws->ew_slots_p;
     A.n_sk_chunks = n_sk;
-    A.S = static_cast<double2 *>(ws->ew_S.ptr);
-    A.n_k_chunks = n_kc;
-    A.kpart_g = static_cast<double *>(ws->ew_kpg.ptr);
-    A.kpart_p = static_cast<double *>(ws->ew_kpp.ptr);
+    A.sk_chunk = chunk;
+    A.sk_part = static_cast<double *>(ws->ew_skp.ptr);
+    A.dest = static_cast<const EwaldDest *>(ws->ew_dest.ptr);
+    A.table = static_cast<double *>(ws->ew_table.ptr);
+    A.tiles = static_cast<const EwaldColTile *>(ws->ew_tiles.ptr);
+    // the bounds of 1, 2, 4, ... ranges lie one after another
+    A.range = static_cast<const int32_t *>(ws->ew_range.ptr) + ((1 << lg) - 1 + lg);
+    A.n_ranges = n_ranges;
+    A.kpart = static_cast<double *>(ws->ew_kp.ptr);
     A.msum = static_cast<double *>(ws->ew_msum.ptr);
+    A.self_c = ws->ew_self;
+    A.bg_c = ws->ew_bg;
     A.gk = static_cast<double *>(ws->ew_g.ptr);
-    A.pk = static_cast<double *>(ws->ew_p.ptr);
+    A.pk = want_p ? static_cast<double *>(ws->ew_p.ptr) : nullptr;
     A.mass_ready = false;
     return COLATUS_OK;
 }
 
 // The symmetric work list (parts of 256) of one box, whatever the tile
-// options say: the periodic real-space loop runs on it.  FP32 pairs of a box
-// whose pair items would leave most SIMDs with at most one wave take the
-// one-sided list: eight items of 64 particles for each pair of parts, which
-// evaluate every pair twice, with the same bits, in eight times the waves (a
-// SIMD pairs the FP32 instructions of two waves, never of one).  A mixed
+// options say: the periodic real-space loop runs on it.  A box whose pair
+// items would leave most SIMDs with at most one wave takes the one-sided list:
+// eight items of 64 particles for each pair of parts, which evaluate every
+// pair twice in eight times the waves (FP32 pairs with the same bits; a SIMD
+// pairs the FP32 instructions of two waves, never of one).  A mixed
 // evaluation, pair items / one-sided: 1500 particles 195 / 132 us, 4000 (184
 // waves) 173 / 110, 8000 (624) 204 / 190, 12 000 (1269) 258 / 265, 16 000
 // 336 / 374.
 constexpr int64_t kOneSidedWaves = 1024;
+// FP64 pairs (not paired by the hardware, longer items): 1500 particles 273 /
+// 132 us, 4000 281 / 148, 6000 (372 waves) 301 / 225, 8000 (624) 314 / 337.
+constexpr int64_t kOneSidedWaves64 = 512;
 
 int prepare_periodic_worklist(Workspace *ws, int64_t N, double eps, int precision, hipStream_t s)
 {
@@ -1592,7 +1708,7 @@ int prepare_periodic_worklist(Workspace *ws, int64_t N, double eps, int precisio
     b.eps = {eps};
     b.max_n = N;
     TileCfg c = symmetric_cfg(b, 4, 64);
-    if (precision != COLATUS_FP64 && symmetric_waves(b) < kOneSidedWaves)
+    if (symmetric_waves(b) < (precision == COLATUS_FP64 ? kOneSidedWaves64 : kOneSidedWaves))
         c.group = kOneSided;
     WorkList *wl = nullptr;
     CHECK_RC(select_worklist(ws, b, N, c, s, wl));
@@ -2251,21 +2367,22 @@ int colatus_forces_periodic(const double *x, const double *m, int64_t N, double 
     if (phi)
         CHECK_RC(ensure(ws->part_phi, (size_t)wl.max_slices * N * sizeof(double)));
     EwaldArgs E;
-    CHECK_RC(ewald_args(ws, x, m, N, E));
+    CHECK_RC(ewald_args(ws, x, m, N, phi != nullptr, E));
+    CHECK_HIP(launch_ewald_kspace(E, s));
     CHECK_HIP(launch_ewald_real(precision, phi != nullptr, x, m, N,
                                 static_cast<const WorkItem *>(wl.d_items.ptr), (int)wl.items.size(),
                                 static_cast<double *>(ws->part.ptr),
                                 phi ? static_cast<double *>(ws->part_phi.ptr) : nullptr, nullptr,
-                                box, ws->ew_alpha, s));
+                                box, ws->ew_alpha,
+                                static_cast<const double *>(ws->ew_poly.ptr), s));
     const ExtField none{};
     CHECK_HIP(launch_forces_finalize(precision, nullptr,
                                      static_cast<const IntBlock *>(wl.d_blocks.ptr),
                                      (int)wl.blocks.size(), static_cast<const double *>(ws->part.ptr),
                                      phi ? static_cast<const double *>(ws->part_phi.ptr) : nullptr,
                                      slot_mode_of(wl, precision), x, m, N, G, G / (a * a * a),
-                                     none, 1.0 / (a * a * a), acc, phi, s));
-    CHECK_HIP(launch_ewald_kspace(E, s));
-    CHECK_HIP(launch_ewald_add(E.gk, E.pk, N, G, 1.0 / (a * a * a), acc, phi, s));
+                                     none, 1.0 / (a * a * a), acc, phi, s, nullptr, nullptr,
+                                     nullptr, E.gk, E.pk));
     return COLATUS_OK;
 }
 
@@ -2303,7 +2420,7 @@ int colatus_run_periodic(double *x, double *v, const double *m, int64_t N, doubl
         CHECK_RC(ensure(ws->diag_out, (size_t)rows * sizeof(colatus_diag)));
     }
     EwaldArgs E;
-    CHECK_RC(ewald_args(ws, x, m, N, E));
+    CHECK_RC(ewald_args(ws, x, m, N, with_diag, E));
     StepCoef *coef = static_cast<StepCoef *>(ws->coef.ptr);
     double *p = static_cast<double *>(ws->p.ptr);
     CHECK_HIP(launch_coefficients(H0, Om_R, Om_M, Om_K, Om_L, a_begin, a_end, n_steps, first_step,
@@ -2315,7 +2432,8 @@ int colatus_run_periodic(double *x, double *v, const double *m, int64_t N, doubl
                                     static_cast<const WorkItem *>(wl.d_items.ptr),
                                     (int)wl.items.size(), static_cast<double *>(ws->part.ptr),
                                     with_diag ? static_cast<double *>(ws->part_phi.ptr) : nullptr,
-                                    step_inc, box, ws->ew_alpha, s));
+                                    step_inc, box, ws->ew_alpha,
+                                    static_cast<const double *>(ws->ew_poly.ptr), s));
         CHECK_HIP(launch_ewald_kspace(E, s));
         return COLATUS_OK;
     };

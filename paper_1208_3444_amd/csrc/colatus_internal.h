@@ -193,6 +193,8 @@ hipError_t launch_zero_counter(int *counter, hipStream_t stream);
 // acc = scale * sum_s part[s] + inv_a3 f_att(x), phi = -G (sum_s part_phi[s] -
 // m/eps) + phi_att(x).  With kick_v: also the closing half kick of a cached
 // step from that acc, kick_v = (kick_p + k2 acc) / a1^2 (kick_coef[0]).
+// ewald_g / ewald_p (or null): the reciprocal-space field and potential part
+// of periodic boundaries, added to the slots' sums.
 hipError_t launch_forces_finalize(int precision, const double *box_mass,
                                   const IntBlock *blocks, int n_blocks,
                                   const double *part, const double *part_phi, int slot_mode,
@@ -200,7 +202,9 @@ hipError_t launch_forces_finalize(int precision, const double *box_mass,
                                   double scale, const ExtField &ext, double inv_a3,
                                   double *acc, double *phi, hipStream_t stream,
                                   const double *kick_p = nullptr, double *kick_v = nullptr,
-                                  const StepCoef *kick_coef = nullptr);
+                                  const StepCoef *kick_coef = nullptr,
+                                  const double *ewald_g = nullptr,
+                                  const double *ewald_p = nullptr);
 
 // out = G * sum_s part[s] - S M(d) lam (attractor) for n_cot cotangents
 // ([n_cot][3][N]).
@@ -362,45 +366,70 @@ hipError_t launch_ftle(const double *grad, const int64_t *idx, int T, int64_t N,
 // Real-space part: the symmetric work items (parts of 256, R = 4, one wave),
 // each pair's nearest image, Plummer pair less the smooth long-range part
 // (see pair_sweep.hip); slots as the symmetric loop's (FP32 for FP32 pairs,
-// FP64 otherwise), masses included (readers take no common mass).
+// FP64 otherwise), masses included (readers take no common mass).  alpha:
+// the Gaussian splitting of FP32 pairs; poly: the window's polynomials of FP64
+// pairs (ewald_window.h), in units of this box (device).
 hipError_t launch_ewald_real(int precision, bool with_phi, const double *x, const double *m,
                              int64_t N, const WorkItem *items, int n_items, double *part,
                              double *part_phi, int64_t *step_inc, double L, double alpha,
-                             hipStream_t stream);
+                             const double *poly, hipStream_t stream);
 
-// A run of consecutive n_z of one reciprocal-space column (nx, ny), its k
-// values stored from k0 on.
-constexpr int kEwaldSegLen = 16;
-struct EwaldSeg {
-    int nx, ny, z0, cnt, k0;
+// Reciprocal space (ewald.hip).  Limits of its kernels: q = |n_z| below
+// kEwQ (two matrix tiles of eight), n_max at most kEwMaxN (phases in
+// registers), eight waves of kEwPairs row tiles with both q tiles and
+// kEwSingles with the first.
+constexpr int kEwQ = 16;
+constexpr int kEwMaxN = 14;
+constexpr int kEwPairs = 4, kEwSingles = 2;
+constexpr int kEwMaxTiles = 8 * (kEwPairs + kEwSingles);
+// Four columns (n_x, n_y) of the half of k-space, a column tile of the field
+// kernel: ks steps of two q each reach its longest column's n_z; the table
+// holds kEwQ / 2 steps of 64 doubles for every tile.
+struct EwaldColTile {
+    int ks;
+    int nx[4], ny[4];
+};
+// Where an element of the structure factors goes in the table, and with what
+// weight: the V entry and the V' entry (-1: padding).
+struct EwaldDest {
+    int32_t v, z;
+    double wv, wz;
+};
+// The structure-factor kernel's columns, in row tiles of eight, longest
+// columns first (the first n_pairs tiles reach q >= 8), and each wave's tiles
+// (-1: none).
+struct EwaldSkPlan {
+    int n_pairs;
+    int16_t slots[8][kEwPairs + kEwSingles];
+    int2 cols[kEwMaxTiles * 8];
 };
 
 struct EwaldArgs {
     const double *x, *m;
     int64_t N;
-    double L, alpha;
-    const EwaldSeg *segs;  // [n_segs], k0 consecutive
-    const EwaldSeg *segs_sk;  // [n_segs] the same segments, longest first (structure factors)
-    int n_segs, K;
-    const double *coef;    // [K]: 2 (4 pi / L^3) exp(-k^2 / 4 alpha^2) / k^2
-    double2 *sk_part;      // [n_sk_chunks][K]
+    double L;
+    const EwaldSkPlan *sk_plan;
+    int sk_slots_p;        // row tiles with both q tiles a wave holds (at most kEwPairs)
+    int n_units;           // 256-element accumulator tiles
     int n_sk_chunks;
-    double2 *S;            // [K]: W(k) = coef(k) S(k), the weighted structure factor
-    int n_k_chunks;        // ranges of segments for the per-particle sums
-    double *kpart_g;       // [n_k_chunks][3][N]
-    double *kpart_p;       // [n_k_chunks][N]
+    int64_t sk_chunk;      // particles per chunk (n_sk_chunks of them cover N)
+    double *sk_part;       // [n_sk_chunks][n_units][256]
+    const EwaldDest *dest; // [n_units][256]
+    double *table;         // the field's operands; padding stays zero
+    const EwaldColTile *tiles;
+    const int32_t *range;  // [n_ranges + 1] tile bounds of the field kernel's ranges
+    int n_ranges;
+    double *kpart;         // [n_ranges][4][N]
     double *msum;          // [1]: total mass
     bool mass_ready;       // msum already holds the masses' sum (a run's later steps)
+    double self_c, bg_c;   // self term and background constants
     double *gk;            // [3][N] out: reciprocal field (no G)
-    double *pk;            // [N] out: reciprocal potential part + self and background terms
+    double *pk;            // [N] out: reciprocal potential part + self and background
+                           // terms, or null (not wanted)
 };
 // The reciprocal-space field and potential part of every particle, with the
 // self and background constants (ewald.hip).
 hipError_t launch_ewald_kspace(const EwaldArgs &args, hipStream_t stream);
-
-// acc += G inv_a3 gk; phi += -G pk (phi may be null).
-hipError_t launch_ewald_add(const double *gk, const double *pk, int64_t N, double G,
-                            double inv_a3, double *acc, double *phi, hipStream_t stream);
 
 // p[0..n) = value (a fill kernel; graph-safe).
 hipError_t launch_fill(double *p, int64_t n, double value, hipStream_t stream);

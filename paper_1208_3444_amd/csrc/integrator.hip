@@ -601,7 +601,8 @@ __global__ __launch_bounds__(kFinalizeThreads) void forces_finalize_kernel(
     const double *__restrict__ x, const double *__restrict__ m, int64_t N, double G,
     double scale, ExtField ext, double inv_a3, double *__restrict__ acc,
     double *__restrict__ phi, const double *__restrict__ kick_p, double *__restrict__ kick_v,
-    const StepCoef *__restrict__ kick_coef)
+    const StepCoef *__restrict__ kick_coef, const double *__restrict__ ewald_g,
+    const double *__restrict__ ewald_p)
 {
     __shared__ double shs[4][kSliceGroups][kIntBlock];
     const IntBlock blk = blocks[blockIdx.x];
@@ -616,6 +617,8 @@ __global__ __launch_bounds__(kFinalizeThreads) void forces_finalize_kernel(
         phe = ext_pull(ext, x[i], x[N + i], x[2 * N + i], blk.eps, f);
     if (lead && valid)
         for (int c = 0; c < 3; ++c) {
+            if (ewald_g)
+                g[c] += ewald_g[(int64_t)c * N + i];
             const double gc = scale * g[c] + inv_a3 * f[c];
             acc[(int64_t)c * N + i] = gc;
             if (kick_v) {
@@ -630,8 +633,11 @@ __global__ __launch_bounds__(kFinalizeThreads) void forces_finalize_kernel(
         __syncthreads();
         double t[1];
         slot_sum<1>(part_phi, slot_mode, i, blk.n_slices, N, N, valid, shs, mbox, t);
-        if (lead && valid)
+        if (lead && valid) {
+            if (ewald_p)
+                t[0] += ewald_p[i];
             phi[i] = -G * (t[0] - self_potential(precision, m[i], blk.eps, mbox)) + phe;
+        }
     }
 }
 
@@ -1041,11 +1047,12 @@ hipError_t launch_forces_finalize(int precision, const double *box_mass, const I
                                   int slot_mode, const double *x, const double *m, int64_t N,
                                   double G, double scale, const ExtField &ext, double inv_a3,
                                   double *acc, double *phi, hipStream_t stream,
-                                  const double *kick_p, double *kick_v, const StepCoef *kick_coef)
+                                  const double *kick_p, double *kick_v, const StepCoef *kick_coef,
+                                  const double *ewald_g, const double *ewald_p)
 {
     hipLaunchKernelGGL(forces_finalize_kernel, dim3(n_blocks), dim3(kFinalizeThreads), 0, stream,
                        precision, box_mass, blocks, part, part_phi, slot_mode, x, m, N, G, scale,
-                       ext, inv_a3, acc, phi, kick_p, kick_v, kick_coef);
+                       ext, inv_a3, acc, phi, kick_p, kick_v, kick_coef, ewald_g, ewald_p);
     return hipGetLastError();
 }
 

@@ -34,6 +34,7 @@
 // pulls work items from a device counter until none are left (every
 // workgroup's last fetch sees the counter past the end and exits).
 #include "colatus_internal.h"
+#include "ewald_window.h"
 
 #include <math.h>
 #include <type_traits>
@@ -46,9 +47,6 @@ enum AccMode { kDirect = 0, kTwoSum = 1, kFold64 = 2 };
 template <typename T> struct V4;
 template <> struct V4<float> { using type = float4; };
 template <> struct V4<double> { using type = double4; };
-
-__device__ __forceinline__ float rsqrt_t(float s) { return __builtin_amdgcn_rsqf(s); }
-__device__ __forceinline__ double rsqrt_t(double s) { return rsqrt_refined(s); }
 
 // The hardware estimate of s^{-1/2} alone, and the weights made from it: the
 // pair loops issue the estimates of several pairs back to back and finish
@@ -90,7 +88,11 @@ __device__ __forceinline__ float in_vgpr(float c)
     asm("" : "+v"(c));
     return c;
 }
-__device__ __forceinline__ double in_vgpr(double c) { return c; }
+__device__ __forceinline__ double in_vgpr(double c)
+{
+    asm("" : "+v"(c));
+    return c;
+}
 // c ? v : other with v computed in every lane (a select, never a branch
 // around v's computation).
 __device__ __forceinline__ float select_value(bool c, float v, float other)
@@ -877,6 +879,39 @@ __device__ __forceinline__ void wave_centre(const double (&tx)[R], const double 
     cz = uniform(0.5 * (v[2] + v[5]));
 }
 
+// The bounding box [lo, hi] of one wave's targets, in every lane (scalar
+// registers); targets not to be counted repeat a valid one.
+template <int R>
+__device__ __forceinline__ void wave_box(const double (&tx)[R], const double (&ty)[R],
+                                         const double (&tz)[R], double (&lo)[3], double (&hi)[3])
+{
+    lo[0] = hi[0] = tx[0];
+    lo[1] = hi[1] = ty[0];
+    lo[2] = hi[2] = tz[0];
+#pragma unroll
+    for (int r = 1; r < R; ++r) {
+        lo[0] = fmin(lo[0], tx[r]);
+        lo[1] = fmin(lo[1], ty[r]);
+        lo[2] = fmin(lo[2], tz[r]);
+        hi[0] = fmax(hi[0], tx[r]);
+        hi[1] = fmax(hi[1], ty[r]);
+        hi[2] = fmax(hi[2], tz[r]);
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            lo[q] = fmin(lo[q], __shfl_xor(lo[q], off, 64));
+            hi[q] = fmax(hi[q], __shfl_xor(hi[q], off, 64));
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        lo[q] = uniform(lo[q]);
+        hi[q] = uniform(hi[q]);
+    }
+}
+
 // One slot value of particle i: FP32 sums stored as FP32 without the box
 // mass; FP64 sums stored multiplied by it (scale, 1 when the masses differ).
 template <typename T, bool PHI>
@@ -1104,7 +1139,7 @@ __device__ __forceinline__ void sym_adj_chunk(T sx, T sy, T sz, T sm, T slx, T s
                                               const T (&lky)[R], const T (&lkz)[R], T eps2,
                                               T (&ax)[R], T (&ay)[R], T (&az)[R])
 {
-    const T minus3 = in_vgpr((T)-3.0);
+    const T minus3 = sizeof(T) == 4 ? in_vgpr((T)-3.0) : (T)-3.0;
     if constexpr (!EQM)
         sm = wave_rotate_back(sm);
     slx = wave_rotate_back(slx);
@@ -1374,7 +1409,7 @@ __device__ __forceinline__ void adjoint_tile(const V *__restrict__ tile,
     // sources per batch: four FP32 pairs' estimates in one burst (FP64 instructions
     // are never paired, and batching them measured 1 % slower)
     constexpr int U = sizeof(T) == 4 ? 4 / R : 1;
-    const T minus3 = in_vgpr((T)-3);
+    const T minus3 = sizeof(T) == 4 ? in_vgpr((T)-3) : (T)-3;
     for (int j0 = 0; j0 < nt; j0 += U) {
         T dx[U][R], dy[U][R], dz[U][R], s[U][R], y[U][R], mj[U];
 #pragma unroll
@@ -1851,54 +1886,44 @@ hipError_t dispatch_adj(const TileCfg &cfg, bool mask, const double *x, const do
 // each unordered pair evaluated once and applied to both particles: the
 // term changes sign when the two particles swap).  Per pair, with d the
 // nearest image of x_j - x_k, r = |d|:
-//   w   = (r^2 + eps^2)^{-3/2} - P(alpha r) r^{-3},  P(u) = erf(u) - (2u / sqrt(pi)) e^{-u^2}
-//   psi = (r^2 + eps^2)^{-1/2} - erf(alpha r) / r
+//   w   = (r^2 + eps^2)^{-3/2} - P(r) r^{-3}
+//   psi = (r^2 + eps^2)^{-1/2} - Phi(r) / r
 // i.e. the Plummer pair of Eq. (1) less the smooth long-range part that the
-// reciprocal-space sum carries; the other images are negligible (alpha is
-// chosen so that the real-space kernel is below the precision's resolution
-// at half the box).  r == 0 (a part's own particle, or coincident
-// particles): w = 0 and psi = (eps^2)^{-1/2} (0 at eps == 0), the value the
-// open-box loop gives its self pair and the O(N) kernels remove.
+// reciprocal-space sum carries; the other images are negligible (the short-range
+// kernel ends, to the precision's resolution, at half the box).  FP32 pairs:
+// Phi = erf(alpha r), P = erf(u) - (2u / sqrt(pi)) e^{-u^2}, u = alpha r.  FP64
+// pairs: the prolate window (ewald_window.h), whose Phi / r and P / r^3 are
+// polynomials in r^2 up to r_c = L / 2 and 1 / r and 1 / r^3 beyond.  r == 0 (a
+// part's own particle, or coincident particles): w = 0 and psi = (eps^2)^{-1/2}
+// (0 at eps == 0), the value the open-box loop gives its self pair and the
+// O(N) kernels remove.
 // FP64 pairs take coordinates relative to the item's first target, each
 // wrapped to its nearest image before the subtraction, and wrap the pair's
 // separation once more.  FP32 pairs take 32-bit fixed-point coordinates
 // (below).  Masses multiply every term (missing particles have mass 0), and
 // the slots hold them: readers are given no common mass.
 // ---------------------------------------------------------------------------
-template <typename T> struct EwaldReal {
-    T L, invL, alpha, c2;  // c2 = 2 / sqrt(pi)
+struct EwaldReal {
+    double L, invL;
+    double rc2;          // r_c^2
+    double tscale;       // -2 / r_c^2: t = 1 + tscale r^2
+    const double *poly;  // device: P r^{-3} in powers of t (kWindowDegree + 1), then
+                         // Phi r^{-1} (kWindowDegree + 2)
 };
 
-__device__ __forceinline__ float rint_t(float u) { return rintf(u); }
-__device__ __forceinline__ double rint_t(double u) { return rint(u); }
-
-// erf(u) and exp(-u^2) for u >= 0 (FP64 pairs): the math library's.
-__device__ __forceinline__ void erf_gauss(double u, double &erf_u, double &gauss)
+// s^{-1/2} and s^{-3/2} from y = v_rsq_f64(s), e = 1 - s y^2 (|e| < 1.2e-7): two
+// terms of (1 - e)^{-1/2} and (1 - e)^{-3/2}, within rounding of exact.
+__device__ __forceinline__ double rsqrt_exact(double s, double y)
 {
-    erf_u = erf(u);
-    gauss = exp(-u * u);
+    const double e = fma(-s, y * y, 1.0);
+    return fma(y * e, fma(0.375, e, 0.5), y);
 }
-
-template <typename T, bool PHI>
-__device__ __forceinline__ void ewald_pair(T dx, T dy, T dz, T eps2, const EwaldReal<T> &E,
-                                           T &w, T &psi)
+__device__ __forceinline__ double rinv3_exact(double s, double y)
 {
-    const T r2 = fma_t(dx, dx, fma_t(dy, dy, dz * dz));
-    const T rs = rsqrt_t(r2 + eps2);
-    if (r2 > (T)0.0) {
-        const T ri = rsqrt_t(r2);
-        const T u = E.alpha * (r2 * ri);
-        T erf_u, gauss;
-        erf_gauss(u, erf_u, gauss);
-        const T P = erf_u - E.c2 * u * gauss;
-        w = rs * (rs * rs) - P * (ri * (ri * ri));
-        if constexpr (PHI)
-            psi = rs - erf_u * ri;
-    } else {
-        w = (T)0.0;
-        if constexpr (PHI)
-            psi = eps2 > (T)0.0 ? rs : (T)0.0;
-    }
+    const double y2 = y * y;
+    const double e = fma(-s, y2, 1.0);
+    const double y3 = y2 * y;
+    return fma(y3 * e, fma(1.875, e, 1.5), y3);
 }
 
 __device__ __forceinline__ double wrap_image(double d, double L)
@@ -1907,36 +1932,117 @@ __device__ __forceinline__ double wrap_image(double d, double L)
 }
 
 // 64 steps of one source chunk (sources travel around the wave as in
-// sym_chunk) against the lane's R targets.
-template <typename T, int R, bool REACT, bool PHI>
-__device__ __forceinline__ void ewald_chunk(T sx, T sy, T sz, T sm, T &qx, T &qy, T &qz, T &qp,
-                                            const T (&xi)[R], const T (&yi)[R],
-                                            const T (&zi)[R], const T (&mi)[R], T eps2,
-                                            const EwaldReal<T> &E, T (&ax)[R], T (&ay)[R],
-                                            T (&az)[R], T (&ap)[R])
+// sym_chunk) against the lane's R targets, FP64.  wx, wy, wz: this axis'
+// separations may exceed half the box (ewald_item) and are wrapped to the
+// nearest image.  A step whose pairs all lie beyond r_c skips the polynomials,
+// one whose pairs all lie within it the second square root.  The polynomials'
+// constants are read from LDS at the start of every step, every lane the
+// same word: kept in registers they take half the waves, and scalar loads in
+// the loop wait too long (20^3 / 32^3 evaluations: 275 / 1304 us so, 258 / 1317
+// kept in registers, 460 / 1577 by scalar loads).  Bound by FP64 issue; with
+// the math library's erf and exp (about 180 issue slots per pair; about 85 now)
+// a 32^3 evaluation took 2.95 ms.
+template <int R, bool REACT, bool PHI>
+__device__ __forceinline__ void ewald_chunk(bool wx, bool wy, bool wz, double sx, double sy, double sz, double sm, double &qx,
+                                            double &qy, double &qz, double &qp,
+                                            const double (&xi)[R], const double (&yi)[R],
+                                            const double (&zi)[R], const double (&mi)[R],
+                                            double eps2, const EwaldReal &E,
+                                            const double *spoly, double (&ax)[R], double (&ay)[R],
+                                            double (&az)[R], double (&ap)[R])
 {
+#pragma unroll 1
     for (int k = 0; k < 64; ++k) {
+        double dx[R], dy[R], dz[R], r2[R], w[R], psi[R], F[R], S[R];
+        bool near = false, far = false;
+        constexpr int kPoly = PHI ? 2 * kWindowDegree + 3 : kWindowDegree + 1;
+        double poly[kPoly];
+        int at = 0;
+        asm volatile("" : "+v"(at));  // read in this step, not before the loop
+#pragma unroll
+        for (int i = 0; i < kPoly; ++i)
+            poly[i] = spoly[at + i];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            T dx = sx - xi[r], dy = sy - yi[r], dz = sz - zi[r];
-            dx = fma_t(-E.L, rint_t(dx * E.invL), dx);
-            dy = fma_t(-E.L, rint_t(dy * E.invL), dy);
-            dz = fma_t(-E.L, rint_t(dz * E.invL), dz);
-            T w, psi;
-            ewald_pair<T, PHI>(dx, dy, dz, eps2, E, w, psi);
-            const T wt = sm * w;
-            ax[r] = fma_t(wt, dx, ax[r]);
-            ay[r] = fma_t(wt, dy, ay[r]);
-            az[r] = fma_t(wt, dz, az[r]);
+            dx[r] = sx - xi[r];
+            dy[r] = sy - yi[r];
+            dz[r] = sz - zi[r];
+        }
+        if (wx)
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                dx[r] = fma(-E.L, rint(dx[r] * E.invL), dx[r]);
+        if (wy)
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                dy[r] = fma(-E.L, rint(dy[r] * E.invL), dy[r]);
+        if (wz)
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                dz[r] = fma(-E.L, rint(dz[r] * E.invL), dz[r]);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            r2[r] = fma(dx[r], dx[r], fma(dy[r], dy[r], dz[r] * dz[r]));
+            near = near || r2[r] < E.rc2;
+            far = far || !(r2[r] < E.rc2);
+            const double s = r2[r] + eps2;
+            const double y = __builtin_amdgcn_rsq(s);
+            w[r] = rinv3_exact(s, y);
             if constexpr (PHI)
-                ap[r] = fma_t(sm, psi, ap[r]);
-            if constexpr (REACT) {
-                const T ws = mi[r] * w;
-                qx = fma_t(-ws, dx, qx);
-                qy = fma_t(-ws, dy, qy);
-                qz = fma_t(-ws, dz, qz);
+                psi[r] = rsqrt_exact(s, y);
+            F[r] = S[r] = 0.0;
+        }
+        if (__any(near)) {
+            double t[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                t[r] = fma(E.tscale, r2[r], 1.0);
+                F[r] = poly[kWindowDegree];
                 if constexpr (PHI)
-                    qp = fma_t(mi[r], psi, qp);
+                    S[r] = poly[2 * kWindowDegree + 2];
+            }
+#pragma unroll
+            for (int i = kWindowDegree - 1; i >= 0; --i)
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    F[r] = fma(F[r], t[r], poly[i]);
+            if constexpr (PHI) {
+#pragma unroll
+                for (int i = kWindowDegree; i >= 0; --i)
+#pragma unroll
+                    for (int r = 0; r < R; ++r)
+                        S[r] = fma(S[r], t[r], poly[kWindowDegree + 1 + i]);
+            }
+        }
+        if (__any(far)) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const double y = __builtin_amdgcn_rsq(r2[r]);
+                const bool in = r2[r] < E.rc2;
+                F[r] = in ? F[r] : rinv3_exact(r2[r], y);
+                if constexpr (PHI)
+                    S[r] = in ? S[r] : rsqrt_exact(r2[r], y);
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const bool nz = r2[r] > 0.0;
+            w[r] = nz ? w[r] - F[r] : 0.0;
+            const double wt = sm * w[r];
+            ax[r] = fma(wt, dx[r], ax[r]);
+            ay[r] = fma(wt, dy[r], ay[r]);
+            az[r] = fma(wt, dz[r], az[r]);
+            if constexpr (PHI) {
+                psi[r] = nz ? psi[r] - S[r] : eps2 > 0.0 ? psi[r] : 0.0;
+                ap[r] = fma(sm, psi[r], ap[r]);
+            }
+            if constexpr (REACT) {
+                const double ws = mi[r] * w[r];
+                qx = fma(-ws, dx[r], qx);
+                qy = fma(-ws, dy[r], qy);
+                qz = fma(-ws, dz[r], qz);
+                if constexpr (PHI)
+                    qp = fma(mi[r], psi[r], qp);
             }
         }
         sx = wave_rotate(sx);
@@ -1954,53 +2060,69 @@ __device__ __forceinline__ void ewald_chunk(T sx, T sy, T sz, T sm, T &qx, T &qy
 }
 
 // One work item of FP64 pairs (kind 0: a pair of parts with the reaction;
-// kind 1: a 64-target piece of a diagonal part).  Slots as the symmetric
-// loop's, FP64, masses included.
-template <typename T, int R, bool REACT, bool PHI>
+// kind 1: 64 targets against a part).  Slots as the symmetric loop's, FP64,
+// masses included.
+template <int R, bool REACT, bool PHI>
 __device__ __forceinline__ void ewald_item(const WorkItem &w, const double *__restrict__ X,
                                            const double *__restrict__ Y,
                                            const double *__restrict__ Z,
                                            const double *__restrict__ m, int64_t N,
                                            double *__restrict__ part,
-                                           double *__restrict__ part_phi, const double L,
-                                           const EwaldReal<T> &E)
+                                           double *__restrict__ part_phi, const EwaldReal &E,
+                                           const double *spoly)
 {
-    static_assert(sizeof(T) == 8, "FP32 pairs take ewald_item_fx");
     const int lane = threadIdx.x & 63;
+    const double L = E.L;
     // reference point: the item's first target (wave-uniform)
     const double cx = X[w.i0], cy = Y[w.i0], cz = Z[w.i0];
-    T xi[R], yi[R], zi[R], mi[R];
-    T ax[R], ay[R], az[R], ap[R];
+    double xi[R], yi[R], zi[R], mi[R];
+    double ax[R], ay[R], az[R], ap[R];
     bool valid[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int64_t i = w.i0 + (int64_t)(r * 64 + lane);
         valid[r] = i < w.i1;
-        if (valid[r]) {
-            xi[r] = (T)wrap_image(X[i] - cx, L);
-            yi[r] = (T)wrap_image(Y[i] - cy, L);
-            zi[r] = (T)wrap_image(Z[i] - cz, L);
-            mi[r] = (T)m[i];
-        } else {
-            xi[r] = yi[r] = zi[r] = mi[r] = (T)0.0;
-        }
-        ax[r] = ay[r] = az[r] = ap[r] = (T)0.0;
+        const int64_t ii = valid[r] ? i : w.i0;
+        xi[r] = wrap_image(X[ii] - cx, L);
+        yi[r] = wrap_image(Y[ii] - cy, L);
+        zi[r] = wrap_image(Z[ii] - cz, L);
+        mi[r] = valid[r] ? m[i] : 0.0;
+        ax[r] = ay[r] = az[r] = ap[r] = 0.0;
     }
-    const T eps2 = (T)w.eps2;
+    // the targets' bounding box: centre b, half extent h.  A source taken at
+    // its image nearest to b is at its nearest image to every target if it lies
+    // within L / 2 - h of b; a chunk whose sources all do needs no wrap on that
+    // axis (about two thirds of the axes with particles in Morton order).  A NaN
+    // compares false and takes the wrap.
+    double lo[3], hi[3];
+    wave_box<R>(xi, yi, zi, lo, hi);
+    const double bx = 0.5 * (lo[0] + hi[0]), by = 0.5 * (lo[1] + hi[1]),
+                 bz = 0.5 * (lo[2] + hi[2]);
+    // a little inside the limit, for the roundings of b and h
+    const double ex = 0.4999999 * L - 0.5 * (hi[0] - lo[0]),
+                 ey = 0.4999999 * L - 0.5 * (hi[1] - lo[1]),
+                 ez = 0.4999999 * L - 0.5 * (hi[2] - lo[2]);
+    const double eps2 = w.eps2;
     const int n_chunks = (int)((w.j1 - w.j0 + 63) / 64);
     for (int c = 0; c < n_chunks; ++c) {
         const int64_t j = w.j0 + (int64_t)c * 64 + lane;
         const bool jv = j < w.j1;
-        T sx = (T)0.0, sy = (T)0.0, sz = (T)0.0, sm = (T)0.0;
+        double sx = bx, sy = by, sz = bz, sm = 0.0;
         if (jv) {
-            sx = (T)wrap_image(X[j] - cx, L);
-            sy = (T)wrap_image(Y[j] - cy, L);
-            sz = (T)wrap_image(Z[j] - cz, L);
-            sm = (T)m[j];
+            // as the targets first, so that a part's own particle is at r = 0
+            sx = wrap_image(X[j] - cx, L);
+            sx -= L * rint((sx - bx) / L);
+            sy = wrap_image(Y[j] - cy, L);
+            sy -= L * rint((sy - by) / L);
+            sz = wrap_image(Z[j] - cz, L);
+            sz -= L * rint((sz - bz) / L);
+            sm = m[j];
         }
-        T qx = (T)0.0, qy = (T)0.0, qz = (T)0.0, qp = (T)0.0;
-        ewald_chunk<T, R, REACT, PHI>(sx, sy, sz, sm, qx, qy, qz, qp, xi, yi, zi, mi, eps2, E,
-                                      ax, ay, az, ap);
+        const bool wx = !__all(fabs(sx - bx) <= ex), wy = !__all(fabs(sy - by) <= ey),
+                   wz = !__all(fabs(sz - bz) <= ez);
+        double qx = 0.0, qy = 0.0, qz = 0.0, qp = 0.0;
+        ewald_chunk<R, REACT, PHI>(wx, wy, wz, sx, sy, sz, sm, qx, qy, qz, qp, xi, yi, zi, mi,
+                                   eps2, E, spoly, ax, ay, az, ap);
         if constexpr (REACT) {
             if (jv) {
                 const int64_t rs = (int64_t)w.rslice;
@@ -2229,8 +2351,8 @@ __device__ __forceinline__ void ewald_react_fx(const WorkItem &w, const double *
                                                const double *__restrict__ Y,
                                                const double *__restrict__ Z,
                                                const double *__restrict__ m, int64_t N,
-                                               double *__restrict__ part,
-                                               double *__restrict__ part_phi, const double sc,
+                                               float *__restrict__ part,
+                                               float *__restrict__ part_phi, const double sc,
                                                const EwaldFx &E)
 {
     const int lane = threadIdx.x & 63;
@@ -2293,12 +2415,11 @@ __device__ __forceinline__ void ewald_react_fx(const WorkItem &w, const double *
         return;
     const double sf = sc * sc;
     const int64_t rs = (int64_t)w.rslice;
-    float *pf = reinterpret_cast<float *>(part);
-    pf[(rs * 3 + 0) * N + j] = (float)(sf * (double)-qx);
-    pf[(rs * 3 + 1) * N + j] = (float)(sf * (double)-qy);
-    pf[(rs * 3 + 2) * N + j] = (float)(sf * (double)-qz);
+    part[(rs * 3 + 0) * N + j] = (float)(sf * (double)-qx);
+    part[(rs * 3 + 1) * N + j] = (float)(sf * (double)-qy);
+    part[(rs * 3 + 2) * N + j] = (float)(sf * (double)-qz);
     if constexpr (PHI)
-        reinterpret_cast<float *>(part_phi)[rs * N + j] = (float)(sc * (double)qp);
+        part_phi[rs * N + j] = (float)(sc * (double)qp);
 }
 
 __device__ __forceinline__ EwaldFx ewald_fx(double eps2, double sc, double alpha)
@@ -2318,8 +2439,8 @@ __device__ __forceinline__ void ewald_item_fx(const WorkItem &w, const double *_
                                               const double *__restrict__ Y,
                                               const double *__restrict__ Z,
                                               const double *__restrict__ m, int64_t N,
-                                              double *__restrict__ part,
-                                              double *__restrict__ part_phi, const double sc,
+                                              float *__restrict__ part,
+                                              float *__restrict__ part_phi, const double sc,
                                               const EwaldFx &E)
 {
     const int lane = threadIdx.x & 63;
@@ -2342,8 +2463,6 @@ __device__ __forceinline__ void ewald_item_fx(const WorkItem &w, const double *_
         }
         ax[r] = ay[r] = az[r] = ap[r] = 0.0f;
     }
-    float *pf = reinterpret_cast<float *>(part);
-    float *pp = reinterpret_cast<float *>(part_phi);
     const int n_chunks = (int)((w.j1 - w.j0 + 63) / 64);
     for (int c = 0; c < n_chunks; ++c) {
         const int64_t j = w.j0 + (int64_t)c * 64 + lane;
@@ -2362,11 +2481,11 @@ __device__ __forceinline__ void ewald_item_fx(const WorkItem &w, const double *_
         if constexpr (REACT) {
             if (jv) {
                 const int64_t rs = (int64_t)w.rslice;
-                pf[(rs * 3 + 0) * N + j] = (float)(sf * (double)qx);
-                pf[(rs * 3 + 1) * N + j] = (float)(sf * (double)qy);
-                pf[(rs * 3 + 2) * N + j] = (float)(sf * (double)qz);
+                part[(rs * 3 + 0) * N + j] = (float)(sf * (double)qx);
+                part[(rs * 3 + 1) * N + j] = (float)(sf * (double)qy);
+                part[(rs * 3 + 2) * N + j] = (float)(sf * (double)qz);
                 if constexpr (PHI)
-                    pp[rs * N + j] = (float)(sc * (double)qp);
+                    part_phi[rs * N + j] = (float)(sc * (double)qp);
             }
         }
     }
@@ -2376,19 +2495,19 @@ __device__ __forceinline__ void ewald_item_fx(const WorkItem &w, const double *_
         if (!valid[r])
             continue;
         const int64_t i = w.i0 + (int64_t)(r * 64 + lane);
-        pf[(slot * 3 + 0) * N + i] = (float)(sf * (double)ax[r]);
-        pf[(slot * 3 + 1) * N + i] = (float)(sf * (double)ay[r]);
-        pf[(slot * 3 + 2) * N + i] = (float)(sf * (double)az[r]);
+        part[(slot * 3 + 0) * N + i] = (float)(sf * (double)ax[r]);
+        part[(slot * 3 + 1) * N + i] = (float)(sf * (double)ay[r]);
+        part[(slot * 3 + 2) * N + i] = (float)(sf * (double)az[r]);
         if constexpr (PHI)
-            pp[slot * N + i] = (float)(sc * (double)ap[r]);
+            part_phi[slot * N + i] = (float)(sc * (double)ap[r]);
     }
 }
 
-template <typename T, bool PHI>
+template <bool PHI>
 __global__ __launch_bounds__(64) void ewald_real_kernel(
     const double *__restrict__ x, const double *__restrict__ m, int64_t N,
-    const WorkItem *__restrict__ items, int n_items, double *__restrict__ part,
-    double *__restrict__ part_phi, int64_t *__restrict__ step_inc, double L, double alpha)
+    const WorkItem *__restrict__ items, int n_items, float *__restrict__ part,
+    float *__restrict__ part_phi, int64_t *__restrict__ step_inc, double L, double alpha)
 {
     const double *X = x, *Y = x + N, *Z = x + 2 * N;
     if (step_inc && blockIdx.x == 0 && threadIdx.x == 0)
@@ -2397,37 +2516,48 @@ __global__ __launch_bounds__(64) void ewald_real_kernel(
     if (it >= n_items)
         return;
     const WorkItem w = items[it];
-    if constexpr (sizeof(T) == 4) {
-        const double sc = 4294967296.0 / L;  // fixed-point units per length
-        const EwaldFx E = ewald_fx(w.eps2, sc, alpha);
-        if (w.kind == 0)
-            ewald_item_fx<4, true, PHI>(w, X, Y, Z, m, N, part, part_phi, sc, E);
-        else if (w.kind == 1)
-            ewald_item_fx<1, false, PHI>(w, X, Y, Z, m, N, part, part_phi, sc, E);
-        else
-            ewald_react_fx<PHI>(w, X, Y, Z, m, N, part, part_phi, sc, E);
-    } else {
-        EwaldReal<T> E;
-        E.L = (T)L;
-        E.invL = (T)(1.0 / L);
-        E.alpha = (T)alpha;
-        E.c2 = (T)1.1283791670955126;  // 2 / sqrt(pi)
-        if (w.kind == 0)
-            ewald_item<T, 4, true, PHI>(w, X, Y, Z, m, N, part, part_phi, L, E);
-        else
-            ewald_item<T, 1, false, PHI>(w, X, Y, Z, m, N, part, part_phi, L, E);
-    }
+    const double sc = 4294967296.0 / L;  // fixed-point units per length
+    const EwaldFx E = ewald_fx(w.eps2, sc, alpha);
+    if (w.kind == 0)
+        ewald_item_fx<4, true, PHI>(w, X, Y, Z, m, N, part, part_phi, sc, E);
+    else if (w.kind == 1)
+        ewald_item_fx<1, false, PHI>(w, X, Y, Z, m, N, part, part_phi, sc, E);
+    else
+        ewald_react_fx<PHI>(w, X, Y, Z, m, N, part, part_phi, sc, E);
 }
 
-template <typename T, bool PHI>
-hipError_t launch_ewald_real_t(const double *x, const double *m, int64_t N,
-                               const WorkItem *items, int n_items, double *part,
-                               double *part_phi, int64_t *step_inc, double L, double alpha,
-                               hipStream_t stream)
+template <bool PHI>
+__global__ __launch_bounds__(64) void ewald_real64_kernel(
+    const double *__restrict__ x, const double *__restrict__ m, int64_t N,
+    const WorkItem *__restrict__ items, int n_items, double *__restrict__ part,
+    double *__restrict__ part_phi, int64_t *__restrict__ step_inc, EwaldReal E)
 {
-    hipLaunchKernelGGL((ewald_real_kernel<T, PHI>), dim3(n_items), dim3(64), 0, stream, x, m, N,
-                       items, n_items, part, part_phi, step_inc, L, alpha);
-    return hipGetLastError();
+    const double *X = x, *Y = x + N, *Z = x + 2 * N;
+    if (step_inc && blockIdx.x == 0 && threadIdx.x == 0)
+        *step_inc += 1;
+    constexpr int kPoly = 2 * kWindowDegree + 3;
+    __shared__ alignas(16) double spoly[kPoly];
+    const int it = (int)blockIdx.x;
+    if (it >= n_items)
+        return;
+    if ((int)threadIdx.x < kPoly)
+        spoly[threadIdx.x] = E.poly[threadIdx.x];
+    __syncthreads();
+    WorkItem w = items[it];
+    if (w.kind == 0) {
+        ewald_item<4, true, PHI>(w, X, Y, Z, m, N, part, part_phi, E, spoly);
+        return;
+    }
+    if (w.kind == 2) {
+        // the other side of a pair: its sources as targets
+        const int64_t i0 = w.i0, i1 = w.i1;
+        w.i0 = w.j0;
+        w.i1 = w.j1;
+        w.j0 = i0;
+        w.j1 = i1;
+        w.slice = w.rslice;
+    }
+    ewald_item<1, false, PHI>(w, X, Y, Z, m, N, part, part_phi, E, spoly);
 }
 
 }  // namespace
@@ -2466,20 +2596,30 @@ hipError_t launch_pair_sweep(int precision, int form, const TileCfg &cfg, bool w
 hipError_t launch_ewald_real(int precision, bool with_phi, const double *x, const double *m,
                              int64_t N, const WorkItem *items, int n_items, double *part,
                              double *part_phi, int64_t *step_inc, double L, double alpha,
-                             hipStream_t stream)
+                             const double *poly, hipStream_t stream)
 {
     if (n_items <= 0)
         return hipSuccess;
-    if (precision == kFP64)
-        return with_phi ? launch_ewald_real_t<double, true>(x, m, N, items, n_items, part,
-                                                            part_phi, step_inc, L, alpha, stream)
-                        : launch_ewald_real_t<double, false>(x, m, N, items, n_items, part,
-                                                             part_phi, step_inc, L, alpha,
-                                                             stream);
-    return with_phi ? launch_ewald_real_t<float, true>(x, m, N, items, n_items, part, part_phi,
-                                                       step_inc, L, alpha, stream)
-                    : launch_ewald_real_t<float, false>(x, m, N, items, n_items, part, part_phi,
-                                                        step_inc, L, alpha, stream);
+    const dim3 grid((unsigned)n_items), block(64);
+    if (precision == kFP64) {
+        const double rc = 0.5 * L;
+        const EwaldReal E{L, 1.0 / L, rc * rc, -2.0 / (rc * rc), poly};
+        if (with_phi)
+            hipLaunchKernelGGL(ewald_real64_kernel<true>, grid, block, 0, stream, x, m, N, items,
+                               n_items, part, part_phi, step_inc, E);
+        else
+            hipLaunchKernelGGL(ewald_real64_kernel<false>, grid, block, 0, stream, x, m, N, items,
+                               n_items, part, part_phi, step_inc, E);
+        return hipGetLastError();
+    }
+    float *pf = reinterpret_cast<float *>(part), *pp = reinterpret_cast<float *>(part_phi);
+    if (with_phi)
+        hipLaunchKernelGGL(ewald_real_kernel<true>, grid, block, 0, stream, x, m, N, items,
+                           n_items, pf, pp, step_inc, L, alpha);
+    else
+        hipLaunchKernelGGL(ewald_real_kernel<false>, grid, block, 0, stream, x, m, N, items,
+                           n_items, pf, pp, step_inc, L, alpha);
+    return hipGetLastError();
 }
 
 // box_mass[b] = the common mass of box b, or NaN if its masses differ (or one
