@@ -332,8 +332,9 @@ int colatus_run_periodic(double *x, double *v, const double *m, int64_t N, doubl
  * (+ out[t][rows/2] for even rows) = sum_n |w[n]|^2.
  *   track: DEVICE [rows][2][3][n_tracers] (as colatus_tracks.out).
  *   out:   DEVICE [n_tracers][rows/2 + 1], written.
- * FP64 throughout; the phase k n is reduced modulo rows exactly before the
- * twiddle factor is formed.  A direct transform: cost ~ rows^2 n_tracers.
+ * FP64 throughout; phases are reduced modulo a turn exactly (in integers)
+ * before a root of unity is formed.  160 to 4096 rows: by FFTs, cost ~
+ * rows log(rows) n_tracers; fewer or more: a direct sum, ~ rows^2 n_tracers.
  * 1 <= rows <= 131072 and 1 <= n_tracers <= 65536, else COLATUS_EINVAL.   */
 int colatus_velocity_spectrum(const double *track, int64_t rows, int32_t n_tracers,
                               int remove_mean, double *out, void *stream);

@@ -2493,7 +2493,7 @@ int colatus_velocity_spectrum(const double *track, int64_t rows, int32_t n_trace
     Workspace *ws = nullptr;
     std::lock_guard<std::mutex> lock(g_mu);
     CHECK_RC(get_workspace(s, ws));
-    CHECK_RC(ensure(ws->twiddle, (size_t)rows * 2 * sizeof(double)));
+    CHECK_RC(ensure(ws->twiddle, velocity_spectrum_scratch(rows)));
     CHECK_HIP(launch_velocity_spectrum(track, rows, n_tracers, remove_mean ? 1 : 0,
                                        static_cast<double *>(ws->twiddle.ptr), out, s));
     return COLATUS_OK;

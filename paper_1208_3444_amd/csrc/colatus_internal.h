@@ -311,9 +311,11 @@ hipError_t launch_track_gather(const double *x, const double *v, int64_t N,
 
 // Velocity periodogram of each tracer over M track rows (spectrum.hip):
 // out[t][k] = (1/M) sum_c |sum_n w_c[n] e^{-2 pi i k n / M}|^2, k <= M/2,
-// w = v (less its mean if remove_mean).  twiddle: [M] double2 scratch.
+// w = v (less its mean if remove_mean).  scratch: velocity_spectrum_scratch(M)
+// bytes, written by every call before it reads them.
+size_t velocity_spectrum_scratch(int64_t M);
 hipError_t launch_velocity_spectrum(const double *track, int64_t M, int32_t T, int remove_mean,
-                                    double *twiddle, double *out, hipStream_t stream);
+                                    double *scratch, double *out, hipStream_t stream);
 
 // Diagnostics row `row` of the state (x, v) at scale factor a_of(row):
 // row 0 -> coef[0].a0, row r > 0 -> coef[r - 1].a1; p = a^2 v; the potential
