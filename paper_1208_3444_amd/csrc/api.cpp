@@ -514,6 +514,45 @@ TileCfg small_boxes_cfg(const Boxes &b, int kind)
     return TileCfg{1, tpb, (int)std::max<int64_t>(1, (b.max_n + tpb - 1) / tpb), 0};
 }
 
+// The adjoint's matrix form (adjoint_matrix.hip), FP64 pairs: its products hold
+// 16 cotangents, up to three times over, at 1607 / 2240 / 3110 us (two steps
+// at N = 8000), where the ordered loop takes 350-390 for four cotangents and
+// 235 for each one left over.  Ordered / matrix there and at N = 32768: 12
+// cotangents 1540 / 1631 and 20930 / 23360; 13, 1777 / 1633 and 24200 / 23400;
+// 16, 1892 / 1647 and 26460 / 23680; 17, 2156 / 2246 and 31570 / 32680; 18, 2392
+// / 2244 and 34680 / 32660; 49, 5633 / 4531 and 85600 / 68700.  A few boxes
+// leave the ordered loop waiting on each launch: 6 cotangents 445 / 179 at
+// N = 500, 521 / 346 at 3000, but 528 / 511 at 4000 and 8 there 402 / 514.
+constexpr int kMatrixSmallBlocks = 48;  // blocks of 64 targets
+
+bool matrix_adjoint(const Boxes &b, int n_cot)
+{
+    if (n_target_blocks(b, 64) <= kMatrixSmallBlocks)
+        return n_cot > 4;
+    return n_cot >= 13 && n_cot != 17;
+}
+
+// Items of 64 targets; as few source slices as fill whole rounds of two blocks
+// per CU to 95 % (or the best of sixteen).
+TileCfg matrix_cfg(const Boxes &b, int n_cu)
+{
+    const int tb = n_target_blocks(b, 64);
+    const int64_t tiles = (b.max_n + 63) / 64, round = 2 * n_cu;
+    int best = 1;
+    double best_fill = 0.0;
+    for (int s = 1; s <= 16 * (1 + (int)(round / tb)) && s <= tiles; ++s) {
+        const int64_t n = (int64_t)tb * s;
+        const double fill = (double)n / (double)((n + round - 1) / round * round);
+        if (fill > best_fill) {
+            best_fill = fill;
+            best = s;
+        }
+        if (best_fill >= 0.95)
+            break;
+    }
+    return TileCfg{1, 64, best, 3};
+}
+
 // Built-in heuristic: forward sweeps use the symmetric form (each unordered
 // pair once, one wave per item, four targets per lane), measured at 32^3
 // 1.36x (FP32 pairs) and 1.41x (FP64) faster than the ordered form, in 2x2
@@ -522,6 +561,8 @@ TileCfg small_boxes_cfg(const Boxes &b, int kind)
 // both unless the boxes are too small to fill the GPU with its items.
 TileCfg heuristic_cfg(const Boxes &b, int precision, int kind, int n_cu, int n_cot = 1)
 {
+    if (kind == 1 && precision == COLATUS_FP64 && matrix_adjoint(b, n_cot))
+        return matrix_cfg(b, n_cu);
     if (symmetric_waves(b) < kSmallSymWaves)
         return small_boxes_cfg(b, kind);
     if (b.max_n <= kSymMaxN && kind == 0)
@@ -559,7 +600,7 @@ TileCfg apply_overrides(TileCfg c, int kind, int precision, const Boxes &b, int 
         if (want == 2) {
             c = kind == 0 ? grouped_cfg(b) : symmetric_cfg(b, 4, 64);
         } else {
-            if (c.form == 2)
+            if (c.form >= 2)
                 c = ordered_cfg(b, precision, kind, n_cu);
             c.form = want;
         }
@@ -592,6 +633,8 @@ bool cfg_supported(const TileCfg &c, int kind, int precision)
         return ((c.R == 4 || c.R == 8) && c.tpb == 64) || (c.R == 4 && c.tpb == 128);
     if (kind == 1 && c.form == 2)
         return c.R == 4 && c.tpb == 64;
+    if (kind == 1 && c.form == 3)
+        return fp64 && c.R == 1 && c.tpb == 64 && c.slices >= 1;
     if (kind == 0)
         return (c.R == 1 || c.R == 2 || c.R == 4) && (c.tpb == 128 || c.tpb == 256) &&
                c.slices >= 1 && (c.form == 0 || c.form == 1);

@@ -122,7 +122,7 @@ struct TileCfg {
     int R;        // targets per lane
     int tpb;      // threads per block (= sources per LDS tile in forms 0, 1)
     int slices;   // source slices per box (form 2: parts of R * tpb particles)
-    int form;     // FP32 pair-loop form (see launch_pair_sweep); 0 for FP64
+    int form;     // pair-loop form (see launch_pair_sweep); 3: the adjoint's matrix form
     int group = 0; // form 2 with R = 4, tpb = 64: 1 = 2x2 groups of part pairs
                    // per workgroup of four waves (pair_sweep_sym_grp_kernel),
                    // kOneSided = both sides of a pair as items of their own
@@ -181,6 +181,12 @@ hipError_t launch_adjoint_sweep(int precision, const TileCfg &cfg, bool mask_sel
                                 const WorkItem *items, int n_items, int *counter,
                                 bool persistent, const double *box_mass, double *part,
                                 hipStream_t stream);
+
+// The same sum on the FP64 matrix instruction (form 3; items of at most 64
+// targets; adjoint_matrix.hip).  FP64 slots, masses included.
+hipError_t launch_adjoint_matrix(bool mask_self, const double *x, const double *m, int64_t N,
+                                 int n_cot, const double *lam, const WorkItem *items, int n_items,
+                                 double *part, hipStream_t stream);
 
 // Sets *counter = 0 (graph-safe replacement for a memset node).
 hipError_t launch_zero_counter(int *counter, hipStream_t stream);

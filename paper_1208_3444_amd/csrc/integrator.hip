@@ -654,7 +654,8 @@ __global__ __launch_bounds__(kFinalizeThreads) void vjp_finalize_kernel(
     const bool valid = i < blk.i1;
     const bool lead = threadIdx.x < kIntBlock;
     const double mbox = box_mass_of(box_mass, blk.box);
-    for (int c = 0; c < n_cot; ++c) {
+    {
+        const int c = (int)blockIdx.y;  // one cotangent per block
         double w[3];
         slot_sum<3>(part, slot_mode, (int64_t)c * 3 * N + i, blk.n_slices,
                     (int64_t)n_cot * 3 * N, N, valid, shs, mbox, w);
@@ -696,7 +697,8 @@ __global__ __launch_bounds__(kFinalizeThreads) void adjoint_update_kernel(
     const bool valid = i < blk.i1;
     const bool lead = threadIdx.x < kIntBlock;
     const double mbox = box_mass_of(box_mass, blk.box);
-    for (int c = 0; c < n_cot; ++c) {
+    {
+        const int c = (int)blockIdx.y;  // one cotangent per block
         double w[3];
         slot_sum<3>(part, slot_mode, (int64_t)c * 3 * N + i, blk.n_slices,
                     (int64_t)n_cot * 3 * N, N, valid, shs, mbox, w);
@@ -1061,7 +1063,7 @@ hipError_t launch_vjp_finalize(const IntBlock *blocks, int n_blocks, const doubl
                                const double *lam, const ExtField &ext, int64_t N, int n_cot,
                                double G, double *out, hipStream_t stream)
 {
-    hipLaunchKernelGGL(vjp_finalize_kernel, dim3(n_blocks), dim3(kFinalizeThreads), 0, stream,
+    hipLaunchKernelGGL(vjp_finalize_kernel, dim3(n_blocks, n_cot), dim3(kFinalizeThreads), 0, stream,
                        blocks, part, slot_mode, box_mass, x, lam, ext, N, n_cot, G, out);
     return hipGetLastError();
 }
@@ -1072,7 +1074,7 @@ hipError_t launch_adjoint_update(const IntBlock *blocks, int n_blocks, const dou
                                  double G, double cw, double *lam_x, double *lam_p,
                                  int do_drift, double dnext, hipStream_t stream)
 {
-    hipLaunchKernelGGL(adjoint_update_kernel, dim3(n_blocks), dim3(kFinalizeThreads), 0, stream,
+    hipLaunchKernelGGL(adjoint_update_kernel, dim3(n_blocks, n_cot), dim3(kFinalizeThreads), 0, stream,
                        blocks, part, slot_mode, box_mass, x, ext, att_acc, N, n_cot, G, cw, lam_x,
                        lam_p, do_drift, dnext);
     return hipGetLastError();

@@ -2682,6 +2682,11 @@ hipError_t launch_adjoint_sweep(int precision, const TileCfg &cfg, bool mask_sel
 {
     if (n_items <= 0)
         return hipSuccess;
+    if (cfg.form == 3)
+        return precision == kFP64 && cfg.R * cfg.tpb == 64
+                   ? launch_adjoint_matrix(mask_self, x, m, N, n_cot, lam, items, n_items, part,
+                                           stream)
+                   : hipErrorInvalidValue;
     switch (precision) {
     case kFP64:
         return dispatch_adj<double, kDirect>(cfg, mask_self, x, m, N, n_cot, lam, items,
