@@ -18,7 +18,7 @@ INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(ROOT, "_build", "colatus")
 LIB = os.path.join(HERE, "libcolatus.so")
 
-SOURCES = ["pair_sweep.hip", "adjoint_matrix.hip", "integrator.hip", "spectrum.hip",
+SOURCES = ["pair_sweep.hip", "small_box.hip", "adjoint_matrix.hip", "integrator.hip", "spectrum.hip",
            "ewald.hip", "noalloc.hip", "api.cpp"]
 ARCH = "gfx950"
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

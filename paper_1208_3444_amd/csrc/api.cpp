@@ -170,6 +170,7 @@ struct WorkList {
     std::vector<IntBlock> blocks;
     std::vector<int32_t> box_first_block;
     int max_slices = 0;
+    int64_t max_box = 0;  // particles of the largest box
     Buffer d_items, d_blocks, d_box_first, d_off;
     uint64_t used = 0;  // last use (workspace clock), for eviction
     bool matches(const std::vector<int64_t> &o, const std::vector<double> &e, int64_t n,
@@ -514,6 +515,25 @@ TileCfg small_boxes_cfg(const Boxes &b, int kind)
     return TileCfg{1, tpb, (int)std::max<int64_t>(1, (b.max_n + tpb - 1) / tpb), 0};
 }
 
+// The form of small boxes (small_box.hip), general ordered loop / small form, us:
+// FP32 pairs, one block per CU (their LDS leaves no room for two) and one pass
+// of its waves: forces at N = 1000 20.5 / 10.5, 4096 20.6 / 11.9, 5000 24.9 /
+// 30.4; a run's step at 1000 13.6 / 13.5, 4096 16.7 / 15.6, 5000 24 / 34.
+// FP64 pairs, up to three blocks per CU: forces at 1000 20.7 / 10.8, 6144 39.0 /
+// 30.4, 8000 51.6 / 48.9 but with unequal masses and the potential 57.2 / 61.5;
+// a run's step at 1000 14.9 / 10.3, 4096 21.8 / 19.3.
+bool small_form(const Boxes &b, int precision, int n_cu)
+{
+    if (precision == COLATUS_FP64)
+        return n_target_blocks(b, kSmallT64) <= kSmallBlocks64 * n_cu;
+    return b.max_n <= kSmallTiles * kSmallTile && n_target_blocks(b, kSmallT32) <= n_cu;
+}
+
+TileCfg small_form_cfg(int precision)
+{
+    return TileCfg{precision == COLATUS_FP64 ? kSmallT64 : kSmallT32, kSmallTile, 1, 4};
+}
+
 // The adjoint's matrix form (adjoint_matrix.hip), FP64 pairs: its products hold
 // 16 cotangents, up to three times over, at 1607 / 2240 / 3110 us (two steps
 // at N = 8000), where the ordered loop takes 350-390 for four cotangents and
@@ -564,7 +584,8 @@ TileCfg heuristic_cfg(const Boxes &b, int precision, int kind, int n_cu, int n_c
     if (kind == 1 && precision == COLATUS_FP64 && matrix_adjoint(b, n_cot))
         return matrix_cfg(b, n_cu);
     if (symmetric_waves(b) < kSmallSymWaves)
-        return small_boxes_cfg(b, kind);
+        return kind == 0 && small_form(b, precision, n_cu) ? small_form_cfg(precision)
+                                          : small_boxes_cfg(b, kind);
     if (b.max_n <= kSymMaxN && kind == 0)
         return grouped_cfg(b);
     if (b.max_n <= kSymMaxN && n_cot <= kSymMaxCot)
@@ -592,6 +613,10 @@ TileCfg symmetric_cfg(const Boxes &b, int R, int tpb)
 
 TileCfg apply_overrides(TileCfg c, int kind, int precision, const Boxes &b, int n_cu)
 {
+    // the small form has no shape of its own to choose, and no work queue
+    if (c.form == 4 && (g_opt.pair_form >= 0 || g_opt.tile_r > 0 || g_opt.tile_tpb > 0 ||
+                        g_opt.tile_slices > 0 || g_opt.persistent))
+        c = small_boxes_cfg(b, kind);
     // the adjoint and FP64 have one ordered loop: form 1 means form 0 there
     int want = (int)g_opt.pair_form;
     if (want == 1 && (kind == 1 || precision == COLATUS_FP64))
@@ -631,6 +656,9 @@ bool cfg_supported(const TileCfg &c, int kind, int precision)
         return (c.R == 4 && c.tpb == 64) || (c.R == 2 && c.tpb == 128);
     if (kind == 0 && c.form == 2)
         return ((c.R == 4 || c.R == 8) && c.tpb == 64) || (c.R == 4 && c.tpb == 128);
+    if (c.form == 4)
+        return kind == 0 && c.R == (fp64 ? kSmallT64 : kSmallT32) &&
+               c.tpb == kSmallTile;
     if (kind == 1 && c.form == 2)
         return c.R == 4 && c.tpb == 64;
     if (kind == 1 && c.form == 3)
@@ -864,6 +892,7 @@ void build_worklist(const Boxes &b, int64_t N, const TileCfg &cfg, WorkList &wl)
     wl.blocks.clear();
     wl.box_first_block.clear();
     wl.max_slices = 0;
+    wl.max_box = b.max_n;
     if (cfg.form == 2 && cfg.group == 1) {
         build_symmetric_groups(b, cfg, wl);
         return;
@@ -872,7 +901,7 @@ void build_worklist(const Boxes &b, int64_t N, const TileCfg &cfg, WorkList &wl)
         build_symmetric_items(b, cfg, wl);
         return;
     }
-    const int ti = cfg.R * cfg.tpb;
+    const int ti = cfg.form == 4 ? cfg.R : cfg.R * cfg.tpb;
     const int nb = (int)b.eps.size();
     for (int box = 0; box < nb; ++box) {
         const int64_t o0 = b.off[box], o1 = b.off[box + 1], nbx = o1 - o0;
@@ -1030,6 +1059,44 @@ int run_integrate(const IntegrateArgs &A, hipStream_t s)
     return COLATUS_OK;
 }
 
+SmallArgs small_args(const WorkList &wl, int precision, const double *x, const double *m,
+                     int64_t N)
+{
+    SmallArgs A{};
+    A.x = x;
+    A.m = m;
+    A.N = N;
+    A.items = static_cast<const WorkItem *>(wl.d_items.ptr);
+    A.mode = kSmallSums;
+    A.precision = precision;
+    return A;
+}
+
+// Small boxes: the forces in the sweep's own launch, bracketed by the timer if
+// enabled.  Its blocks read x and m until the last of them has written.
+int run_small_forces(const WorkList &wl, bool mask, const SmallArgs &A, hipStream_t s)
+{
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    if (g_opt.timer) {
+        e0 = take_event();
+        e1 = take_event();
+    }
+    if (e0)
+        CHECK_HIP(hipEventRecord(e0, s));
+    CHECK_HIP(launch_small_box(wl.cfg, A.phi != nullptr, mask, wl.max_box, (int)wl.items.size(),
+                               A, s));
+    if (e1) {
+        CHECK_HIP(hipEventRecord(e1, s));
+        g_timer[0].push_back({e0, e1});
+    }
+    return COLATUS_OK;
+}
+
+bool overlap(const double *a, int64_t na, const double *b, int64_t nb)
+{
+    return a && b && a < b + nb && b < a + na;
+}
+
 // Forward pair sweep on the workspace's buffers, with the timer if enabled.
 int run_forward_sweep(Workspace *ws, const WorkList &wl, int precision, bool phi,
                       bool mask, const double *x, const double *m, int64_t N, hipStream_t s,
@@ -1044,7 +1111,15 @@ int run_forward_sweep(Workspace *ws, const WorkList &wl, int precision, bool phi
         CHECK_HIP(launch_zero_counter(work_counter(ws), s));
     if (e0)
         CHECK_HIP(hipEventRecord(e0, s));
-    CHECK_HIP(launch_pair_sweep(precision, wl.cfg.form, wl.cfg, phi, mask, x, m, N,
+    if (wl.cfg.form == 4) {
+        SmallArgs A = small_args(wl, precision, x, m, N);
+        A.box_mass = static_cast<const double *>(ws->box_mass.ptr);
+        A.part = static_cast<double *>(ws->part.ptr);
+        A.part_phi = phi ? static_cast<double *>(ws->part_phi.ptr) : nullptr;
+        A.step_inc = step_inc;
+        CHECK_HIP(launch_small_box(wl.cfg, phi, mask, wl.max_box, (int)wl.items.size(), A, s));
+    } else
+        CHECK_HIP(launch_pair_sweep(precision, wl.cfg.form, wl.cfg, phi, mask, x, m, N,
                                 static_cast<const WorkItem *>(wl.d_items.ptr),
                                 (int)wl.items.size(), work_counter(ws), g_opt.persistent != 0,
                                 static_cast<const double *>(ws->box_mass.ptr),
@@ -2111,6 +2186,8 @@ int colatus_tile_config(int64_t N, int precision, int kind, int32_t out[4])
     auto it = g_tuned.find(key);
     TileCfg c = it != g_tuned.end() ? it->second : heuristic_cfg(b, precision, kind, n_cu);
     c = apply_overrides(c, kind, precision, b, n_cu);
+    if (c.form == 4)  // adds the tiles and slices of this shape
+        c = small_boxes_cfg(b, kind);
     out[0] = c.R;
     out[1] = c.tpb;
     out[2] = c.slices;
@@ -2176,13 +2253,26 @@ int colatus_forces(const double *x, const double *m, int64_t N, double eps, doub
     CHECK_RC(get_workspace(s, ws));
     CHECK_RC(prepare_worklist(ws, 0, b, N, precision, x, m, 1, s));
     const WorkList &wl = *ws->fwd;
+    bool mask = false;
+    for (double e : b.eps)
+        mask = mask || e == 0.0;
+    // one launch, unless the results replace what its blocks still read
+    if (wl.cfg.form == 4 && !overlap(acc, 3 * N, x, 3 * N) && !overlap(acc, 3 * N, m, N) &&
+        !overlap(phi, N, x, 3 * N) && !overlap(phi, N, m, N)) {
+        SmallArgs A = small_args(wl, precision, x, m, N);
+        A.mode = kSmallForces;
+        A.G = G;
+        A.scale = G / (a * a * a);
+        A.inv_a3 = 1.0 / (a * a * a);
+        A.ext = ext;
+        A.acc = acc;
+        A.phi = phi;
+        return run_small_forces(wl, mask, A, s);
+    }
     CHECK_RC(prepare_box_mass(ws, wl, m, s));
     CHECK_RC(ensure(ws->part, (size_t)wl.max_slices * 3 * N * sizeof(double)));
     if (phi)
         CHECK_RC(ensure(ws->part_phi, (size_t)wl.max_slices * N * sizeof(double)));
-    bool mask = false;
-    for (double e : b.eps)
-        mask = mask || e == 0.0;
     CHECK_RC(run_forward_sweep(ws, wl, precision, phi != nullptr, mask, x, m, N, s, true));
     CHECK_HIP(launch_forces_finalize(precision, static_cast<const double *>(ws->box_mass.ptr),
                                      static_cast<const IntBlock *>(wl.d_blocks.ptr),
@@ -2367,18 +2457,38 @@ int colatus_step(double *x, double *v, const double *m, int64_t N, double eps, d
     CHECK_RC(get_workspace(s, ws));
     CHECK_RC(prepare_worklist(ws, 0, b, N, precision, x, m, 1, s));
     const WorkList &wl = *ws->fwd;
-    CHECK_RC(prepare_box_mass(ws, wl, m, s));
     const size_t n3 = 3 * (size_t)N;
     CHECK_RC(ensure(ws->coef, sizeof(StepCoef)));
     CHECK_RC(ensure(ws->p, n3 * sizeof(double)));
-    CHECK_RC(ensure(ws->part, (size_t)wl.max_slices * n3 * sizeof(double)));
     bool mask = false;
     for (double e : b.eps)
         mask = mask || e == 0.0;
     StepCoef *coef = static_cast<StepCoef *>(ws->coef.ptr);
     double *p = static_cast<double *>(ws->p.ptr);
-    CHECK_HIP(launch_coefficients(H0, Om_R, Om_M, Om_K, Om_L, a, a_next, 1, 0, 1, 0, coef, s));
-    CHECK_HIP(launch_cached_kick(0, x, v, p, g_cache, N, coef, s));
+    // the force and the closing kick in one launch, unless the results replace
+    // what its blocks still read
+    const bool small = wl.cfg.form == 4 && !overlap(g_cache, 3 * N, x, 3 * N) &&
+                       !overlap(g_cache, 3 * N, m, N) && !overlap(v, 3 * N, x, 3 * N) &&
+                       !overlap(v, 3 * N, m, N);
+    if (!small) {
+        CHECK_RC(prepare_box_mass(ws, wl, m, s));
+        CHECK_RC(ensure(ws->part, (size_t)wl.max_slices * n3 * sizeof(double)));
+    }
+    CHECK_HIP(launch_step_begin(H0, Om_R, Om_M, Om_K, Om_L, a, a_next, x, v, p, g_cache, N, coef,
+                                s));
+    if (small) {
+        SmallArgs A = small_args(wl, precision, x, m, N);
+        A.mode = kSmallForces;
+        A.G = G;
+        A.scale = G;
+        A.inv_a3 = 1.0;
+        A.ext = ext;
+        A.acc = g_cache;
+        A.kick_p = p;
+        A.kick_v = v;
+        A.kick_coef = coef;
+        return run_small_forces(wl, mask, A, s);
+    }
     CHECK_RC(run_forward_sweep(ws, wl, precision, false, mask, x, m, N, s, true));
     // g at the new positions into the cache (the comoving sum: a = 1), and
     // the closing half kick from it in the same kernel

@@ -122,7 +122,8 @@ struct TileCfg {
     int R;        // targets per lane
     int tpb;      // threads per block (= sources per LDS tile in forms 0, 1)
     int slices;   // source slices per box (form 2: parts of R * tpb particles)
-    int form;     // pair-loop form (see launch_pair_sweep); 3: the adjoint's matrix form
+    int form;     // pair-loop form (see launch_pair_sweep); 3: the adjoint's matrix form,
+                  // 4: small boxes (R targets per block)
     int group = 0; // form 2 with R = 4, tpb = 64: 1 = 2x2 groups of part pairs
                    // per workgroup of four waves (pair_sweep_sym_grp_kernel),
                    // kOneSided = both sides of a pair as items of their own
@@ -187,6 +188,37 @@ hipError_t launch_adjoint_sweep(int precision, const TileCfg &cfg, bool mask_sel
 hipError_t launch_adjoint_matrix(bool mask_self, const double *x, const double *m, int64_t N,
                                  int n_cot, const double *lam, const WorkItem *items, int n_items,
                                  double *part, hipStream_t stream);
+
+// Forward sweep of small boxes (form 4, small_box.hip): items of kSmallT targets
+// against their whole box, the sums finished in the block.  mode kSmallSums
+// writes them as the one slot of an ordered sweep (part, and part_phi if not
+// null); kSmallForces writes acc (and phi if not null) as the forces' finalising
+// kernel does, with the closing kick of a step (v = (p + k2 g) / a1^2) if kick_v
+// is not null.  box_mass null: the blocks find it themselves.
+constexpr int kSmallT32 = 16, kSmallT64 = 8;  // targets per block, FP32 and FP64 pairs
+constexpr int kSmallTile = 128;               // sources per tile (cfg.tpb)
+constexpr int kSmallTiles = 32;               // tiles per box at most, FP32 pairs
+constexpr int kSmallBlocks64 = 3;             // blocks per CU at most, FP64 pairs
+constexpr int kSmallWaves = 8;                // waves per block at most, FP32 pairs
+enum SmallMode { kSmallSums = 0, kSmallForces = 1 };
+struct SmallArgs {
+    const double *x, *m;
+    int64_t N;
+    const WorkItem *items;
+    const double *box_mass;
+    int mode, precision;
+    double *part, *part_phi;
+    int64_t *step_inc;
+    double G, scale, inv_a3;
+    ExtField ext;
+    double *acc, *phi;
+    const double *kick_p;
+    double *kick_v;
+    const StepCoef *kick_coef;
+};
+// max_n: the largest box.
+hipError_t launch_small_box(const TileCfg &cfg, bool with_phi, bool mask_self, int64_t max_n,
+                            int n_items, const SmallArgs &args, hipStream_t stream);
 
 // Sets *counter = 0 (graph-safe replacement for a memset node).
 hipError_t launch_zero_counter(int *counter, hipStream_t stream);
@@ -300,11 +332,11 @@ struct HEArgs {
 // opening half drift unless last.
 hipError_t launch_he_step(const HEArgs &args, hipStream_t stream);
 
-// One step with a cached force g (colatus_step with g_cache), coefficients
-// coef[0]: mode 0 = opening kick and drift (p from v), mode 1 = closing kick
-// and v from p.
-hipError_t launch_cached_kick(int mode, double *x, double *v, double *p, const double *g,
-                              int64_t N, const StepCoef *coef, hipStream_t stream);
+// One step from a to a_next with a cached force g (colatus_step with g_cache):
+// its coefficients into coef[0], the opening kick (p from v) and the drift.
+hipError_t launch_step_begin(double H0, double OmR, double OmM, double OmK, double OmL, double a,
+                             double a_next, double *x, const double *v, double *p,
+                             const double *g, int64_t N, StepCoef *coef, hipStream_t stream);
 
 // ---- tracer tracks ---------------------------------------------------------
 // slot[i] = -1 for all N particles, then slot[idx[t]] = t.

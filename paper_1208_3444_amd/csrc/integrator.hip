@@ -4,6 +4,7 @@
 // traffic (or launch latency at small N): each reads and writes each
 // particle's FP64 state once, coalesced, in structure-of-arrays planes.
 #include "colatus_internal.h"
+#include "device_math.h"
 
 #include "colatus.h"
 
@@ -64,12 +65,30 @@ __device__ void time_integrals(const Cosmo &c, double s0, double s1, double out[
         out[q] = 0.5 * h * acc[q];
 }
 
-__global__ void coefficients_kernel(Cosmo c, double a_begin, double a_end, int64_t n_steps,
-                                    int64_t first, int64_t last, int half_time, StepCoef *coef)
+// Orders the lanes' LDS accesses within a wave (no instruction is needed: a
+// wave's LDS operations complete in order).
+__device__ __forceinline__ void wave_lds_fence()
 {
-    const int64_t n = first + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= last)
-        return;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Working space of the sixteen lanes that share one step.
+struct CoefShared {
+    double wh[2][8], ia[2][8];  // weight / H and 1 / a at the nodes of each half step
+    double out[2][3];           // time_integrals of each half step
+    double half_h, acc[3];      // of the first: 0.5 h and the sums it multiplies
+};
+
+// Coefficients of step n by sixteen lanes (l = 0..15 of one wave), the same
+// numbers as time_integrals over each half step gives: a lane evaluates one
+// node of one half, and one lane per integral adds the nodes in order.  One
+// lane alone takes 6.3 us over its chain of exponentials, roots and divisions.
+// ah and Hh are left NaN.
+__device__ StepCoef step_coefficients(const Cosmo &c, double a_begin, double a_end,
+                                      int64_t n_steps, int64_t n, int l, CoefShared &sh)
+{
     StepCoef s;
     if (c.H0 == 0.0) {
         const double dt = a_end / (double)n_steps;
@@ -82,31 +101,83 @@ __global__ void coefficients_kernel(Cosmo c, double a_begin, double a_end, int64
         s.a1 = a;
         s.ah = a;
         s.Hh = 0.0;
-    } else {
-        const double delta = log(a_end / a_begin) / (double)n_steps;
-        const double a0 = a_begin * exp((double)n * delta);
-        const double ah = a_begin * exp(((double)n + 0.5) * delta);
-        const double a1 = (n + 1 == n_steps) ? a_end : a_begin * exp((double)(n + 1) * delta);
-        const double s0 = log(a0), sh = log(ah), s1 = log(a1);
-        double lo[3], hi[3];
-        time_integrals(c, s0, sh, lo);
-        time_integrals(c, sh, s1, hi);
-        s.k1 = lo[1];
-        s.k2 = hi[1];
-        s.d = lo[2] + hi[2];
-        s.dt = lo[0] + hi[0];
-        s.a0 = a0;
-        s.a1 = a1;
-        // only the Eqs. (3)-(5) scheme reads ah and Hh
-        s.ah = NAN;
-        s.Hh = NAN;
-        if (!half_time) {
-            coef[n - first] = s;
-            return;
-        }
+        return s;
+    }
+    const double delta = log(a_end / a_begin) / (double)n_steps;
+    const double a0 = a_begin * exp((double)n * delta);
+    const double ah = a_begin * exp(((double)n + 0.5) * delta);
+    const double a1 = (n + 1 == n_steps) ? a_end : a_begin * exp((double)(n + 1) * delta);
+    const int half = l >> 3, e = l & 7;
+    const double sm = log(ah), so = log(half ? a1 : a0);
+    const double sb = half ? sm : so, se = half ? so : sm;
+    const double span = se - sb;
+    int nsub = (int)ceil(fabs(span) / 0.05);
+    if (nsub < 1)
+        nsub = 1;
+    const double h = span / nsub;
+    const double x = e < 2   ? 0.18343464249564978
+                     : e < 4 ? 0.52553240991632899
+                     : e < 6 ? 0.79666647741362673
+                             : 0.96028985649753618;
+    const double wt = e < 2   ? 0.36268378337836177
+                      : e < 4 ? 0.31370664587788705
+                      : e < 6 ? 0.22238103445337434
+                              : 0.10122853629037669;
+    const double sgn = e & 1 ? 0.5 : -0.5;
+    double acc = 0.0;
+    for (int k = 0; k < nsub; ++k) {
+        const double mid = sb + (k + 0.5) * h;
+        const double a = exp(fma(sgn * h, x, mid));
+        sh.wh[half][e] = wt / hubble(c, a);
+        sh.ia[half][e] = 1.0 / a;
+        wave_lds_fence();
+        if (e < 3)
+            for (int q = 0; q < 8; ++q) {
+                const double wh = sh.wh[half][q], ia = sh.ia[half][q];
+                acc = e == 0 ? acc + wh : fma(e == 1 ? wh : wh * ia, ia, acc);
+            }
+        wave_lds_fence();
+    }
+    if (e < 3) {
+        sh.out[half][e] = 0.5 * h * acc;
+        if (half == 0)
+            sh.acc[e] = acc;
+    }
+    if (l == 0)
+        sh.half_h = 0.5 * h;
+    wave_lds_fence();
+    s.k1 = sh.out[0][1];
+    s.k2 = sh.out[1][1];
+    s.d = fma(sh.half_h, sh.acc[2], sh.out[1][2]);
+    s.dt = fma(sh.half_h, sh.acc[0], sh.out[1][0]);
+    s.a0 = a0;
+    s.a1 = a1;
+    // only the Eqs. (3)-(5) scheme reads ah and Hh
+    s.ah = NAN;
+    s.Hh = NAN;
+    return s;
+}
+
+// Four steps per wave.
+__global__ __launch_bounds__(64) void coefficients_kernel(Cosmo c, double a_begin, double a_end,
+                                                          int64_t n_steps, int64_t first,
+                                                          int64_t last, int half_time,
+                                                          StepCoef *coef)
+{
+    __shared__ CoefShared sh[4];
+    const int grp = (int)threadIdx.x >> 4, l = (int)threadIdx.x & 15;
+    const int64_t n = first + 4 * (int64_t)blockIdx.x + grp;
+    if (n >= last)
+        return;
+    StepCoef s = step_coefficients(c, a_begin, a_end, n_steps, n, l, sh[grp]);
+    if (l != 0)
+        return;
+    if (half_time && c.H0 != 0.0) {
         // half time of Eqs. (3)-(5): solve int_{s0}^{u} ds / H = dt / 2 for
         // u = ln a by Newton's method (derivative 1/H), from the ln-a midpoint
-        double u = sh;
+        const double delta = log(a_end / a_begin) / (double)n_steps;
+        const double s0 = log(s.a0);
+        double u = log(a_begin * exp(((double)n + 0.5) * delta));
         for (int it = 0; it < 8; ++it) {
             double t[3];
             time_integrals(c, s0, u, t);
@@ -136,28 +207,38 @@ __global__ void convert_kernel(int mode, const double *__restrict__ src, double 
     }
 }
 
-// One kick-drift-kick step with the force at its start given (the step
-// with a cached force): mode 0, p = a_n^2 v, p += k1 g, x += d p; mode 1,
-// p += k2 g, v = p / a_{n+1}^2.  The same operations, in the same order, as
-// the conversion and integrate kernels of a run.  Elementwise over [3][N].
-__global__ void cached_kick_kernel(int mode, double *__restrict__ x, double *__restrict__ v,
-                                   double *__restrict__ p, const double *__restrict__ g,
-                                   int64_t n3, const StepCoef *__restrict__ coef)
+// Opening of one kick-drift-kick step with the force g at its start given
+// (colatus_step with a cached force): p = a_n^2 v, p += k1 g, x += d p, the same
+// operations, in the same order, as the conversion and integrate kernels of a
+// run.  Elementwise over [3][N].  Every block works the step's coefficients out
+// by itself (a launch of their own, waiting on 16 lanes, costs more); block 0
+// leaves them in coef[0] for the closing kick.
+__global__ __launch_bounds__(256) void step_begin_kernel(
+    Cosmo c, double a_begin, double a_end, double *__restrict__ x, const double *__restrict__ v,
+    double *__restrict__ p, const double *__restrict__ g, int64_t n3, StepCoef *__restrict__ coef)
 {
+    __shared__ CoefShared sh;
+    __shared__ StepCoef scf;
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n3)
-        return;
-    const StepCoef cf = coef[0];
-    // explicit FMAs: the run's kernels contract their updates the same way
-    if (mode == 0) {
-        const double p0 = cf.a0 * cf.a0 * v[i];
-        const double pi = fma(cf.k1, g[i], p0);
-        x[i] = fma(cf.d, pi, x[i]);
-        p[i] = pi;
-    } else {
-        const double pi = fma(cf.k2, g[i], p[i]);
-        v[i] = pi / (cf.a1 * cf.a1);
+    const bool valid = i < n3;
+    const double vi = valid ? v[i] : 0.0, gi = valid ? g[i] : 0.0, xi = valid ? x[i] : 0.0;
+    if (threadIdx.x < 16) {
+        const StepCoef s = step_coefficients(c, a_begin, a_end, 1, 0, (int)threadIdx.x, sh);
+        if (threadIdx.x == 0) {
+            scf = s;
+            if (blockIdx.x == 0)
+                coef[0] = s;
+        }
     }
+    __syncthreads();
+    if (!valid)
+        return;
+    const StepCoef cf = scf;
+    // explicit FMAs: the run's kernels contract their updates the same way
+    const double p0 = cf.a0 * cf.a0 * vi;
+    const double pi = fma(cf.k1, gi, p0);
+    x[i] = fma(cf.d, pi, xi);
+    p[i] = pi;
 }
 
 // Deterministic tree sum of kDiagW values over the first kIntBlock threads
@@ -187,71 +268,6 @@ __device__ void block_sum_rows(double (&v)[kDiagW], double (*sh)[kIntBlock])
 __device__ __forceinline__ bool finite3(double a, double b, double c)
 {
     return isfinite(a) && isfinite(b) && isfinite(c);
-}
-
-// The potential sweep includes the self pair j == k, whose term is exactly
-// m_k * rsqrt(eps^2) as the sweep computed it (zero separation); subtract
-// that same value, rounded the same way, so no FP32-vs-FP64 residue of a
-// large self term is left in phi.  Equal-mass boxes (mbox not NaN) were
-// summed without m and scaled by mbox in FP64.  With eps == 0 the sweep
-// masks the self pair.
-__device__ __forceinline__ double self_potential(int precision, double m, double eps,
-                                                 double mbox)
-{
-    if (!(eps > 0.0))
-        return 0.0;
-    const double eps2 = eps * eps;
-    if (precision == kFP64)
-        return m * rsqrt_refined(eps2);
-    const float r = __builtin_amdgcn_rsqf((float)eps2);
-    if (!isnan(mbox))
-        return mbox * (double)r;
-    return (double)((float)m * r);
-}
-
-__device__ __forceinline__ double box_mass_of(const double *box_mass, int box)
-{
-    return box_mass ? box_mass[box] : NAN;
-}
-
-// Eq. (10) attractor at particle position (px, py, pz), softening eps: adds
-// its field S d r^-3 (d = x_psi - x, r^2 = |d|^2 + eps^2) to f and returns
-// its potential -S / r.  FP64 with IEEE square root and division.
-__device__ __forceinline__ double attractor_pull(const ExtField &A, double px, double py,
-                                                 double pz, double eps, double (&f)[3])
-{
-    const double dx = A.x - px, dy = A.y - py, dz = A.z - pz;
-    const double s = dx * dx + dy * dy + dz * dz + eps * eps;
-    const double r = sqrt(s);
-    const double r3 = 1.0 / (s * r);
-    f[0] += A.S * dx * r3;
-    f[1] += A.S * dy * r3;
-    f[2] += A.S * dz * r3;
-    return -A.S / r;
-}
-
-// Background term of Eq. (6): adds b (x - c) to f and returns its potential
-// -b |x - c|^2 / 2.
-__device__ __forceinline__ double background_pull(const ExtField &E, double px, double py,
-                                                  double pz, double (&f)[3])
-{
-    const double dx = px - E.cx, dy = py - E.cy, dz = pz - E.cz;
-    f[0] += E.b * dx;
-    f[1] += E.b * dy;
-    f[2] += E.b * dz;
-    return -0.5 * E.b * (dx * dx + dy * dy + dz * dz);
-}
-
-// Every external term present: field added to f, potential returned.
-__device__ __forceinline__ double ext_pull(const ExtField &E, double px, double py, double pz,
-                                           double eps, double (&f)[3])
-{
-    double ph = 0.0;
-    if (E.on)
-        ph += attractor_pull(E, px, py, pz, eps, f);
-    if (E.bg)
-        ph += background_pull(E, px, py, pz, f);
-    return ph;
 }
 
 // M(d) l with M(d) = r^-3 I - 3 r^-5 d d^T (the attractor's field derivative
@@ -996,7 +1012,7 @@ hipError_t launch_coefficients(double H0, double OmR, double OmM, double OmK, do
 {
     Cosmo c{H0, OmR, OmM, OmK, OmL};
     const int64_t n = last - first;
-    hipLaunchKernelGGL(coefficients_kernel, dim3(blocks_for(n, 64)), dim3(64), 0, stream, c,
+    hipLaunchKernelGGL(coefficients_kernel, dim3(blocks_for(n, 4)), dim3(64), 0, stream, c,
                        a_begin, a_end, n_steps, first, last, half_time, coef);
     return hipGetLastError();
 }
@@ -1125,12 +1141,13 @@ hipError_t launch_he_drift(double *x, const double *v, int64_t N, const StepCoef
     return hipGetLastError();
 }
 
-hipError_t launch_cached_kick(int mode, double *x, double *v, double *p, const double *g,
-                              int64_t N, const StepCoef *coef, hipStream_t stream)
+hipError_t launch_step_begin(double H0, double OmR, double OmM, double OmK, double OmL, double a,
+                             double a_next, double *x, const double *v, double *p,
+                             const double *g, int64_t N, StepCoef *coef, hipStream_t stream)
 {
     const int64_t n3 = 3 * N;
-    hipLaunchKernelGGL(cached_kick_kernel, dim3((unsigned)((n3 + 255) / 256)), dim3(256), 0,
-                       stream, mode, x, v, p, g, n3, coef);
+    hipLaunchKernelGGL(step_begin_kernel, dim3((unsigned)((n3 + 255) / 256)), dim3(256), 0,
+                       stream, Cosmo{H0, OmR, OmM, OmK, OmL}, a, a_next, x, v, p, g, n3, coef);
     return hipGetLastError();
 }
 
