@@ -518,10 +518,10 @@ TileCfg small_boxes_cfg(const Boxes &b, int kind)
 // The form of small boxes (small_box.hip), general ordered loop / small form, us:
 // FP32 pairs, one block per CU (their LDS leaves no room for two) and one pass
 // of its waves: forces at N = 1000 20.5 / 10.5, 4096 20.6 / 11.9, 5000 24.9 /
-// 30.4; a run's step at 1000 13.6 / 13.5, 4096 16.7 / 15.6, 5000 24 / 34.
+// 30.4; a run's step at 1000 13.5 / 11.1, 4096 16.8 / 13.1, 5000 24 / 34.
 // FP64 pairs, up to three blocks per CU: forces at 1000 20.7 / 10.8, 6144 39.0 /
 // 30.4, 8000 51.6 / 48.9 but with unequal masses and the potential 57.2 / 61.5;
-// a run's step at 1000 14.9 / 10.3, 4096 21.8 / 19.3.
+// a run's step at 1000 14.9 / 7.3, 4096 21.8 / 16.7, 6144 38.0 / 29.9.
 bool small_form(const Boxes &b, int precision, int n_cu)
 {
     if (precision == COLATUS_FP64)
@@ -1445,6 +1445,38 @@ int enqueue_steps(Workspace *ws, const RunParams &P, const IntegrateArgs &base, 
     return COLATUS_OK;
 }
 
+// A run of small boxes without diagnostics: one launch per grid point, which
+// reads the positions of one buffer and leaves the next ones in the other (the
+// caller's and the workspace's in turn).  Needs the coefficients, the common
+// masses and the track buffers.
+int enqueue_small_run(Workspace *ws, const RunParams &P, const WorkList &wl, bool mask,
+                      int64_t n_steps)
+{
+    hipStream_t s = P.stream;
+    CHECK_RC(ensure(ws->he_x, 3 * (size_t)P.N * sizeof(double)));
+    double *buf[2] = {P.x, static_cast<double *>(ws->he_x.ptr)};
+    SmallArgs A = small_args(wl, P.precision, P.x, P.m, P.N);
+    A.mode = kSmallRun;
+    A.box_mass = static_cast<const double *>(ws->box_mass.ptr);
+    A.G = P.G;
+    A.ext = P.ext;
+    A.p = static_cast<double *>(ws->p.ptr);
+    A.v = P.v;
+    A.coef = static_cast<const StepCoef *>(ws->coef.ptr);
+    A.n_rows = n_steps;
+    A.track_slot = P.trk.n ? static_cast<const int32_t *>(ws->track_slot.ptr) : nullptr;
+    A.track = P.trk.out;
+    A.n_tracers = P.trk.n;
+    for (int64_t k = 0; k <= n_steps; ++k) {
+        TraceRange step("step");
+        A.x = buf[k & 1];
+        A.x_out = k < n_steps ? buf[(k + 1) & 1] : (k & 1) ? P.x : nullptr;
+        A.row = k;
+        CHECK_HIP(launch_small_box(wl.cfg, false, mask, wl.max_box, (int)wl.items.size(), A, s));
+    }
+    return COLATUS_OK;
+}
+
 int run_impl(const RunParams &P, const Boxes &b)
 {
     Workspace *ws = nullptr;
@@ -1475,6 +1507,11 @@ int run_impl(const RunParams &P, const Boxes &b)
     double *p = static_cast<double *>(ws->p.ptr);
     CHECK_HIP(launch_coefficients(P.H0, P.OmR, P.OmM, P.OmK, P.OmL, P.a_begin, P.a_end,
                                   P.n_steps, P.first, P.last, 0, coef, s));
+    if (wl.cfg.form == 4 && !diag && !g_opt.graph && !g_opt.timer && nsteps > 0 &&
+        !overlap(P.v, 3 * P.N, P.x, 3 * P.N)) {
+        CHECK_RC(prepare_tracks(ws, P));
+        return enqueue_small_run(ws, P, wl, mask, nsteps);
+    }
     CHECK_HIP(launch_convert(0, P.v, p, P.N, coef, 0, s));
     CHECK_RC(set_step(ws, P.first, P.first, P.last, s));
     CHECK_RC(run_forward_sweep(ws, wl, P.precision, diag, mask, P.x, P.m, P.N, s, false));

@@ -194,13 +194,16 @@ hipError_t launch_adjoint_matrix(bool mask_self, const double *x, const double *
 // writes them as the one slot of an ordered sweep (part, and part_phi if not
 // null); kSmallForces writes acc (and phi if not null) as the forces' finalising
 // kernel does, with the closing kick of a step (v = (p + k2 g) / a1^2) if kick_v
-// is not null.  box_mass null: the blocks find it themselves.
+// is not null; kSmallRun makes step `row` of a run of n_rows steps (kick, drift,
+// tracks; row 0 takes p from v, row n_rows closes the run and makes v from p) as
+// the integrate and conversion kernels do, its new positions in x_out, which is
+// not x.  box_mass null: the blocks find it themselves.
 constexpr int kSmallT32 = 16, kSmallT64 = 8;  // targets per block, FP32 and FP64 pairs
 constexpr int kSmallTile = 128;               // sources per tile (cfg.tpb)
 constexpr int kSmallTiles = 32;               // tiles per box at most, FP32 pairs
 constexpr int kSmallBlocks64 = 3;             // blocks per CU at most, FP64 pairs
 constexpr int kSmallWaves = 8;                // waves per block at most, FP32 pairs
-enum SmallMode { kSmallSums = 0, kSmallForces = 1 };
+enum SmallMode { kSmallSums = 0, kSmallForces = 1, kSmallRun = 2 };
 struct SmallArgs {
     const double *x, *m;
     int64_t N;
@@ -215,6 +218,12 @@ struct SmallArgs {
     const double *kick_p;
     double *kick_v;
     const StepCoef *kick_coef;
+    double *x_out, *p, *v;
+    const StepCoef *coef;
+    int64_t row, n_rows;
+    const int32_t *track_slot;
+    double *track;
+    int64_t n_tracers;
 };
 // max_n: the largest box.
 hipError_t launch_small_box(const TileCfg &cfg, bool with_phi, bool mask_self, int64_t max_n,

@@ -102,6 +102,27 @@ def test_runs_and_cached_steps(dev, prec):
 
 
 @pytest.mark.parametrize("prec", ["fp64", "mixed_twosum"])
+@pytest.mark.parametrize("first,last", [(0, 1), (0, 2), (3, 8)])
+def test_run_in_one_launch_per_step(dev, prec, first, last):
+    """Odd and even counts (the positions end in either buffer), tracks, ragged
+    boxes; an external term with FP64 pairs (contracted differently)."""
+    off, eps = np.array([0, 200, 203, 1100]), np.array([0.05, 0.1, 0.03])
+    x, m = (to_dev(a, dev) for a in _cloud(1100, False))
+    v = 0.1 * torch.randn(3, 1100, dtype=torch.float64, device=dev,
+                          generator=torch.Generator(dev).manual_seed(2))
+
+    def run():
+        u, w = x.clone(), v.clone()
+        bg = (0.2, (0.0, 0.1, 0.0)) if prec == "fp64" else None
+        _, tr = colatus.run(u, w, m, 0.0, 1.0, inputs.LCDM, 0.2, 1.0, 40, first_step=first,
+                            last_step=last, precision=prec, batch=(off, eps), background=bg,
+                            tracers=[0, 201, 1099])
+        return u, w, tr
+
+    _same(*_both(run), prec)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed_twosum"])
 def test_results_may_replace_the_positions(dev, prec):
     N = 1000
     x, m = (to_dev(a, dev) for a in _cloud(N, True))
