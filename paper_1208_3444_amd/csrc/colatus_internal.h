@@ -170,9 +170,9 @@ hipError_t launch_pair_sweep(int precision, int form, const TileCfg &cfg, bool w
                              hipStream_t stream);
 
 // box_mass[b] = m of box b if all its masses are equal and positive, else NaN
-// (box_offsets: device, n_boxes + 1 entries ending at N).
+// (box_offsets: device, n_boxes + 1 entries ending at N; max_n: the largest box).
 hipError_t launch_box_mass(const double *m, const int64_t *box_offsets, int n_boxes, int64_t N,
-                           double *box_mass, hipStream_t stream);
+                           int64_t max_n, double *box_mass, hipStream_t stream);
 
 // Adjoint pair sweep for n_cot cotangents lam [n_cot][3][N]:
 // part[s][c][3][N] = sum over the item's sources of M(d)(m_k lam_j - m_j lam_k).

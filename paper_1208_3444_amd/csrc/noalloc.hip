@@ -243,7 +243,7 @@ extern "C" int colatus_forces_noalloc(const double *x, const double *m, int64_t 
                        items, blocks, offsets, counter);
     if (hipGetLastError() != hipSuccess)
         return COLATUS_EHIP;
-    if (launch_box_mass(m, offsets, 1, N, box_mass, s) != hipSuccess)
+    if (launch_box_mass(m, offsets, 1, N, N, box_mass, s) != hipSuccess)
         return COLATUS_EHIP;
     TileCfg cfg{4, 64, P, 2};
     cfg.group = 1;
