@@ -1992,30 +1992,30 @@ int adjoint_impl(Workspace *ws, const AdjointParams &P, const Boxes &b)
     A.x = xw;
     for (int64_t n = 0; n < n_steps; ++n) {
         TraceRange step("adjoint forward step");
+        // every sweep but the first advances the step
+        int64_t *inc = n > 0 ? step_counter(ws) : nullptr;
         if (keep_all) {
             // x_n stays in slot n; the step writes x_{n+1} into slot n + 1
-            double *xs = seg + (size_t)n * n3;
-            double *xn = xs + n3;
-            CHECK_RC(run_forward_sweep(ws, wf, precision, false, mask, xs, m, N, s, true));
-            CHECK_HIP(hipMemcpyAsync(xn, xs, n3 * sizeof(double), hipMemcpyDeviceToDevice, s));
-            A.x = xn;
+            A.x = seg + (size_t)n * n3;
+            A.x_out = A.x + n3;
+            CHECK_RC(run_forward_sweep(ws, wf, precision, false, mask, A.x, m, N, s, true, inc));
             CHECK_HIP(launch_integrate(A, s));
-            CHECK_HIP(launch_tick(step_counter(ws), work_counter(ws), s));
             continue;
         }
-        CHECK_RC(run_forward_sweep(ws, wf, precision, false, mask, xw, m, N, s, true));
+        CHECK_RC(run_forward_sweep(ws, wf, precision, false, mask, xw, m, N, s, true, inc));
         if (n % K == 0) {
             double *cx = ck + (size_t)(n / K) * 2 * n3;
             CHECK_HIP(hipMemcpyAsync(cx, xw, n3 * sizeof(double), hipMemcpyDeviceToDevice, s));
             CHECK_HIP(hipMemcpyAsync(cx + n3, p, n3 * sizeof(double), hipMemcpyDeviceToDevice, s));
         }
         CHECK_HIP(launch_integrate(A, s));
-        CHECK_HIP(launch_tick(step_counter(ws), work_counter(ws), s));
     }
     if (keep_all)
         xw = seg + (size_t)n_steps * n3;  // x_N
+    A.x_out = nullptr;
     if (xN || vN) {
-        CHECK_RC(run_forward_sweep(ws, wf, precision, false, mask, xw, m, N, s, true));
+        CHECK_RC(run_forward_sweep(ws, wf, precision, false, mask, xw, m, N, s, true,
+                                   step_counter(ws)));
         A.x = xw;
         CHECK_HIP(launch_integrate(A, s));  // closing half kick at a_end
         if (xN)
@@ -2047,14 +2047,12 @@ int adjoint_impl(Workspace *ws, const AdjointParams &P, const Boxes &b)
             CHECK_RC(set_step(ws, lo, 0, n_steps, s));
         }
         for (int64_t n = lo; n < hi && !keep_all; ++n) {
-            double *xs = seg + (size_t)(n - lo) * n3;
-            double *xn = seg + (size_t)(n - lo + 1) * n3;
-            CHECK_RC(run_forward_sweep(ws, wf, precision, false, mask, xs, m, N, s, true));
-            CHECK_HIP(hipMemcpyAsync(xn, xs, n3 * sizeof(double), hipMemcpyDeviceToDevice, s));
             IntegrateArgs B = A;
-            B.x = xn;
+            B.x = seg + (size_t)(n - lo) * n3;
+            B.x_out = B.x + n3;
+            CHECK_RC(run_forward_sweep(ws, wf, precision, false, mask, B.x, m, N, s, true,
+                                       n > lo ? step_counter(ws) : nullptr));
             CHECK_HIP(launch_integrate(B, s));
-            CHECK_HIP(launch_tick(step_counter(ws), work_counter(ws), s));
         }
         // visit x_n for n = hi .. lo+1 (and lo itself in segment 0): every grid
         // point is visited once, x_hi being the unvisited bottom of the segment above

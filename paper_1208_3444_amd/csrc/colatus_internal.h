@@ -272,7 +272,7 @@ hipError_t launch_convert(int mode, const double *src, double *dst, int64_t N,
                           const StepCoef *coef, int64_t idx, hipStream_t stream);
 
 struct IntegrateArgs {
-    double *x;             // [3][N], in/out
+    double *x;             // [3][N], in/out (in only if x_out is not null)
     double *p;             // [3][N], in/out (canonical momentum a^2 v)
     const double *m;
     const double *part;    // [S][3][N]
@@ -284,8 +284,7 @@ struct IntegrateArgs {
     const StepCoef *coef;  // indexed by (n - first)
     const int64_t *step;   // device run descriptor {n, first, last}: the
                            // absolute step counter n (advanced by the next
-                           // pair sweep or a tick kernel) and the call's step
-                           // range; kept in device memory so that a captured
+                           // pair sweep) and the call's step range; kept in device memory so that a captured
                            // step graph does not depend on the range
     int *work_counter;     // pair-sweep work counter, re-armed here (or null)
     double *diag_part;     // [rows][n_blocks][kDiagW] or null
@@ -302,15 +301,13 @@ struct IntegrateArgs {
     const double *ewald_g = nullptr;
     const double *ewald_p = nullptr;
     double box = 0.0;
+    double *x_out = nullptr; // [3][N]: x_{n+1} is written here instead (n < last)
 };
 // Finalise g(x_n) from the partials, then kick by k2_{n-1} (n > first),
 // record diagnostics of the state at a_n, and (n < last) kick by k1_n and
 // drift by d_n.  Reads n from *step and re-arms the pair-sweep work counter
 // for the sweep that follows (graph-safe, no memset).
 hipError_t launch_integrate(const IntegrateArgs &args, hipStream_t stream);
-
-// *step += 1; *counter = 0.
-hipError_t launch_tick(int64_t *step, int *counter, hipStream_t stream);
 
 // ---- the paper's difference equations, Eqs. (3)-(5) ------------------------
 // x += f * coef[idx].dt * v over all particles (the opening half drift).

@@ -516,9 +516,10 @@ __global__ __launch_bounds__(kFinalizeThreads) void integrate_kernel(IntegrateAr
                 if (A.box > 0.0)
                     xx[c] -= A.box * floor(xx[c] / A.box);
             }
-            A.x[i] = xx[0];
-            A.x[N + i] = xx[1];
-            A.x[2 * N + i] = xx[2];
+            double *xo = A.x_out ? A.x_out : A.x;
+            xo[i] = xx[0];
+            xo[N + i] = xx[1];
+            xo[2 * N + i] = xx[2];
         }
         A.p[i] = p[0];
         A.p[N + i] = p[1];
@@ -534,12 +535,6 @@ __global__ __launch_bounds__(kFinalizeThreads) void integrate_kernel(IntegrateAr
     }
     if (A.work_counter && blockIdx.x == 0 && threadIdx.x == 0)
         *A.work_counter = 0;
-}
-
-__global__ void tick_kernel(int64_t *step, int *counter)
-{
-    *step += 1;
-    *counter = 0;
 }
 
 // One block per box: sum the per-block rows in block order, then the
@@ -1029,12 +1024,6 @@ hipError_t launch_integrate(const IntegrateArgs &args, hipStream_t stream)
 {
     hipLaunchKernelGGL(integrate_kernel, dim3(args.n_blocks), dim3(kFinalizeThreads), 0, stream,
                        args);
-    return hipGetLastError();
-}
-
-hipError_t launch_tick(int64_t *step, int *counter, hipStream_t stream)
-{
-    hipLaunchKernelGGL(tick_kernel, dim3(1), dim3(1), 0, stream, step, counter);
     return hipGetLastError();
 }
 
