@@ -1446,6 +1446,21 @@ int enqueue_steps(Workspace *ws, const RunParams &P, const IntegrateArgs &base, 
     return COLATUS_OK;
 }
 
+// The arguments of a small run's launches, positions, velocities and row aside.
+SmallArgs small_run_args(Workspace *ws, const WorkList &wl, int precision, const double *m,
+                         int64_t N, double G, const ExtField &ext, int64_t n_steps)
+{
+    SmallArgs A = small_args(wl, precision, nullptr, m, N);
+    A.mode = kSmallRun;
+    A.box_mass = static_cast<const double *>(ws->box_mass.ptr);
+    A.G = G;
+    A.ext = ext;
+    A.p = static_cast<double *>(ws->p.ptr);
+    A.coef = static_cast<const StepCoef *>(ws->coef.ptr);
+    A.n_rows = n_steps;
+    return A;
+}
+
 // A run of small boxes without diagnostics: one launch per grid point, which
 // reads the positions of one buffer and leaves the next ones in the other (the
 // caller's and the workspace's in turn).  Needs the coefficients, the common
@@ -1456,15 +1471,8 @@ int enqueue_small_run(Workspace *ws, const RunParams &P, const WorkList &wl, boo
     hipStream_t s = P.stream;
     CHECK_RC(ensure(ws->he_x, 3 * (size_t)P.N * sizeof(double)));
     double *buf[2] = {P.x, static_cast<double *>(ws->he_x.ptr)};
-    SmallArgs A = small_args(wl, P.precision, P.x, P.m, P.N);
-    A.mode = kSmallRun;
-    A.box_mass = static_cast<const double *>(ws->box_mass.ptr);
-    A.G = P.G;
-    A.ext = P.ext;
-    A.p = static_cast<double *>(ws->p.ptr);
+    SmallArgs A = small_run_args(ws, wl, P.precision, P.m, P.N, P.G, P.ext, n_steps);
     A.v = P.v;
-    A.coef = static_cast<const StepCoef *>(ws->coef.ptr);
-    A.n_rows = n_steps;
     A.track_slot = P.trk.n ? static_cast<const int32_t *>(ws->track_slot.ptr) : nullptr;
     A.track = P.trk.out;
     A.n_tracers = P.trk.n;
@@ -1987,41 +1995,65 @@ int adjoint_impl(Workspace *ws, const AdjointParams &P, const Boxes &b)
 
     // ---- forward with checkpoints --------------------------------------
     CHECK_HIP(hipMemcpyAsync(xw, x0, n3 * sizeof(double), hipMemcpyDeviceToDevice, s));
-    CHECK_HIP(launch_convert(0, v0, p, N, coef, 0, s));
-    CHECK_RC(set_step(ws, 0, 0, n_steps, s));
-    A.x = xw;
-    for (int64_t n = 0; n < n_steps; ++n) {
-        TraceRange step("adjoint forward step");
-        // every sweep but the first advances the step
-        int64_t *inc = n > 0 ? step_counter(ws) : nullptr;
-        if (keep_all) {
-            // x_n stays in slot n; the step writes x_{n+1} into slot n + 1
-            A.x = seg + (size_t)n * n3;
-            A.x_out = A.x + n3;
-            CHECK_RC(run_forward_sweep(ws, wf, precision, false, mask, A.x, m, N, s, true, inc));
-            CHECK_HIP(launch_integrate(A, s));
-            continue;
+    if (keep_all && wf.cfg.form == 4 && !g_opt.timer) {
+        // small boxes: a step per launch, from slot n to slot n + 1
+        SmallArgs S = small_run_args(ws, wf, precision, m, N, G, ext, n_steps);
+        S.v = const_cast<double *>(v0);  // read by row 0 alone
+        for (int64_t n = 0; n < n_steps; ++n) {
+            TraceRange step("adjoint forward step");
+            S.x = seg + (size_t)n * n3;
+            S.x_out = seg + (size_t)(n + 1) * n3;
+            S.row = n;
+            CHECK_HIP(launch_small_box(wf.cfg, false, mask, wf.max_box, (int)wf.items.size(), S,
+                                       s));
         }
-        CHECK_RC(run_forward_sweep(ws, wf, precision, false, mask, xw, m, N, s, true, inc));
-        if (n % K == 0) {
-            double *cx = ck + (size_t)(n / K) * 2 * n3;
-            CHECK_HIP(hipMemcpyAsync(cx, xw, n3 * sizeof(double), hipMemcpyDeviceToDevice, s));
-            CHECK_HIP(hipMemcpyAsync(cx + n3, p, n3 * sizeof(double), hipMemcpyDeviceToDevice, s));
+        if (xN || vN) {
+            S.x = seg + (size_t)n_steps * n3;
+            S.x_out = xN;
+            S.v = vN;
+            S.row = n_steps;
+            CHECK_HIP(launch_small_box(wf.cfg, false, mask, wf.max_box, (int)wf.items.size(), S,
+                                       s));
         }
-        CHECK_HIP(launch_integrate(A, s));
-    }
-    if (keep_all)
-        xw = seg + (size_t)n_steps * n3;  // x_N
-    A.x_out = nullptr;
-    if (xN || vN) {
-        CHECK_RC(run_forward_sweep(ws, wf, precision, false, mask, xw, m, N, s, true,
-                                   step_counter(ws)));
+    } else {
+        CHECK_HIP(launch_convert(0, v0, p, N, coef, 0, s));
+        CHECK_RC(set_step(ws, 0, 0, n_steps, s));
         A.x = xw;
-        CHECK_HIP(launch_integrate(A, s));  // closing half kick at a_end
-        if (xN)
-            CHECK_HIP(hipMemcpyAsync(xN, xw, n3 * sizeof(double), hipMemcpyDeviceToDevice, s));
-        if (vN)
-            CHECK_HIP(launch_convert(1, p, vN, N, coef, n_steps - 1, s));
+        for (int64_t n = 0; n < n_steps; ++n) {
+            TraceRange step("adjoint forward step");
+            // every sweep but the first advances the step
+            int64_t *inc = n > 0 ? step_counter(ws) : nullptr;
+            if (keep_all) {
+                // x_n stays in slot n; the step writes x_{n+1} into slot n + 1
+                A.x = seg + (size_t)n * n3;
+                A.x_out = A.x + n3;
+                CHECK_RC(run_forward_sweep(ws, wf, precision, false, mask, A.x, m, N, s, true,
+                                           inc));
+                CHECK_HIP(launch_integrate(A, s));
+                continue;
+            }
+            CHECK_RC(run_forward_sweep(ws, wf, precision, false, mask, xw, m, N, s, true, inc));
+            if (n % K == 0) {
+                double *cx = ck + (size_t)(n / K) * 2 * n3;
+                CHECK_HIP(hipMemcpyAsync(cx, xw, n3 * sizeof(double), hipMemcpyDeviceToDevice, s));
+                CHECK_HIP(hipMemcpyAsync(cx + n3, p, n3 * sizeof(double),
+                                         hipMemcpyDeviceToDevice, s));
+            }
+            CHECK_HIP(launch_integrate(A, s));
+        }
+        if (keep_all)
+            xw = seg + (size_t)n_steps * n3;  // x_N
+        A.x_out = nullptr;
+        if (xN || vN) {
+            CHECK_RC(run_forward_sweep(ws, wf, precision, false, mask, xw, m, N, s, true,
+                                       step_counter(ws)));
+            A.x = xw;
+            CHECK_HIP(launch_integrate(A, s));  // closing half kick at a_end
+            if (xN)
+                CHECK_HIP(hipMemcpyAsync(xN, xw, n3 * sizeof(double), hipMemcpyDeviceToDevice, s));
+            if (vN)
+                CHECK_HIP(launch_convert(1, p, vN, N, coef, n_steps - 1, s));
+        }
     }
 
     // ---- reverse sweep ---------------------------------------------------

@@ -195,7 +195,7 @@ hipError_t launch_adjoint_matrix(bool mask_self, const double *x, const double *
 // null); kSmallForces writes acc (and phi if not null) as the forces' finalising
 // kernel does, with the closing kick of a step (v = (p + k2 g) / a1^2) if kick_v
 // is not null; kSmallRun makes step `row` of a run of n_rows steps (kick, drift,
-// tracks; row 0 takes p from v, row n_rows closes the run and makes v from p) as
+// tracks; row 0 takes p from v, row n_rows closes the run and makes v, if not null, from p) as
 // the integrate and conversion kernels do, its new positions in x_out, which is
 // not x.  box_mass null: the blocks find it themselves.
 constexpr int kSmallT32 = 16, kSmallT64 = 8;  // targets per block, FP32 and FP64 pairs

@@ -10,6 +10,8 @@
 // (FP32 pairs) and 22.8 -> 16.1 (FP64), a cached step of 4096 36 -> 21 us.  A
 // run takes one launch a step instead of two: 1000 particles 13.5 -> 11 us a
 // step (FP64 14.9 -> 7.3), 4096 16.8 -> 13.1 (21.8 -> 16.7).
+// So does the forward pass of an adjoint that keeps every position: five steps
+// and their gradient, 1000 particles, FP32 pairs 323 -> 290 us.
 //
 // FP32 pairs keep the ordered sweep's bits: coordinates relative to the centre
 // of the same tile of targets, one FP32 sum per tile of sources in order, the
@@ -70,7 +72,7 @@ __device__ __forceinline__ void small_finish(const SmallArgs &A, const WorkItem 
                     out[c * A.n_tracers] = x[c];
                     out[(3 + c) * A.n_tracers] = p[c] / (cp.a1 * cp.a1);
                 }
-                if (A.row == A.n_rows)
+                if (A.row == A.n_rows && A.v)
                     A.v[(int64_t)c * N + i] = p[c] / (cp.a1 * cp.a1);
             }
         }

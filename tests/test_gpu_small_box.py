@@ -123,6 +123,25 @@ def test_run_in_one_launch_per_step(dev, prec, first, last):
 
 
 @pytest.mark.parametrize("prec", ["fp64", "mixed_twosum"])
+@pytest.mark.parametrize("n", [1, 6])
+def test_adjoint_forward_in_one_launch_per_step(dev, prec, n):
+    """Every position kept (one launch a step) against checkpoints (two): the
+    same bits, with and without the final state."""
+    N = 1000
+    x, m = (to_dev(a, dev) for a in _cloud(N, False))
+    gen = torch.Generator(dev).manual_seed(3)
+    v, lx, lv = (torch.randn(3, N, dtype=torch.float64, device=dev, generator=gen)
+                 for _ in range(3))
+    out = [colatus.adjoint(x, 0.1 * v, m, 0.05, 1.0, inputs.LCDM, 0.2, 1.0, n, lx, lv,
+                           checkpoint_every=k, precision=prec, return_state=state)
+           for k, state in ((0, True), (n, True), (0, False))]
+    for a, b in zip(out[0], out[1]):
+        assert torch.equal(a, b)
+    for a, b in zip(out[0], out[2]):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed_twosum"])
 def test_results_may_replace_the_positions(dev, prec):
     N = 1000
     x, m = (to_dev(a, dev) for a in _cloud(N, True))
