@@ -1353,7 +1353,7 @@ std::vector<uint64_t> step_graph_key(const Workspace *ws, const RunParams &P,
     const WorkList &wl = *ws->fwd;
     KeyBuilder k;
     // integrate_kernel
-    k.add(A.x); k.add(A.p); k.add(A.m); k.add(A.part); k.add(A.part_phi); k.add(A.blocks);
+    k.add(A.x); k.add(A.p); k.add(A.v); k.add(A.m); k.add(A.part); k.add(A.part_phi); k.add(A.blocks);
     k.add((int64_t)A.n_blocks); k.add(A.N); k.add(A.G); k.add(A.coef); k.add(A.step);
     k.add(A.work_counter); k.add(A.diag_part); k.add((int64_t)A.precision); k.add(A.box_mass);
     k.add((int64_t)A.slot_mode);
@@ -1521,13 +1521,13 @@ int run_impl(const RunParams &P, const Boxes &b)
         CHECK_RC(prepare_tracks(ws, P));
         return enqueue_small_run(ws, P, wl, mask, nsteps);
     }
-    CHECK_HIP(launch_convert(0, P.v, p, P.N, coef, 0, s));
     CHECK_RC(set_step(ws, P.first, P.first, P.last, s));
     CHECK_RC(run_forward_sweep(ws, wl, P.precision, diag, mask, P.x, P.m, P.N, s, false));
 
     IntegrateArgs A;
     A.x = P.x;
     A.p = p;
+    A.v = P.v;
     A.m = P.m;
     A.part = static_cast<const double *>(ws->part.ptr);
     A.part_phi = diag ? static_cast<const double *>(ws->part_phi.ptr) : nullptr;
@@ -1550,7 +1550,6 @@ int run_impl(const RunParams &P, const Boxes &b)
 
     CHECK_RC(enqueue_steps(ws, P, A, mask, nsteps));
     CHECK_RC(run_integrate(A, s));  // closing half kick at a_last (+ diagnostics)
-    CHECK_HIP(launch_convert(1, p, P.v, P.N, coef, nsteps - 1, s));
     if (diag) {
         CHECK_HIP(launch_diag_reduce(static_cast<const double *>(ws->diag_part.ptr), (int)rows,
                                      A.blocks, A.n_blocks, n_boxes,

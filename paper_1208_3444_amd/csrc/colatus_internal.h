@@ -302,6 +302,8 @@ struct IntegrateArgs {
     const double *ewald_p = nullptr;
     double box = 0.0;
     double *x_out = nullptr; // [3][N]: x_{n+1} is written here instead (n < last)
+    double *v = nullptr;     // [3][N]: p is made from v at n = first, and v from p
+                             // at n = last (a launch of its own for each: 3 us)
 };
 // Finalise g(x_n) from the partials, then kick by k2_{n-1} (n > first),
 // record diagnostics of the state at a_n, and (n < last) kick by k1_n and

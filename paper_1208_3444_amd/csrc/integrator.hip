@@ -470,14 +470,25 @@ __global__ __launch_bounds__(kFinalizeThreads) void integrate_kernel(IntegrateAr
                 phs += A.ewald_p[i];
         }
         double g[3] = {A.G * gs[0], A.G * gs[1], A.G * gs[2]};
-        double p[3] = {A.p[i], A.p[N + i], A.p[2 * N + i]};
+        double p[3] = {0.0, 0.0, 0.0};
+        if (A.v && n == first) {  // p = a^2 v, the conversion kernel's product
+            const double a0 = A.coef[0].a0;
+            for (int c = 0; c < 3; ++c)
+                p[c] = a0 * a0 * A.v[c * N + i];
+        } else {
+            for (int c = 0; c < 3; ++c)
+                p[c] = A.p[c * N + i];
+        }
         double xx[3] = {A.x[i], A.x[N + i], A.x[2 * N + i]};
         // external potential (attractor, background: counted once)
         const double phe = ext_pull(A.ext, xx[0], xx[1], xx[2], blk.eps, g);
         if (n > first) {
             const StepCoef cp = A.coef[row - 1];
             for (int c = 0; c < 3; ++c)
-                p[c] += cp.k2 * g[c];
+                p[c] = fma(cp.k2, g[c], p[c]);
+            if (A.v && n == last)
+                for (int c = 0; c < 3; ++c)
+                    A.v[c * N + i] = p[c] / (cp.a1 * cp.a1);
             // tracer row at a_n: v = p / a^2, the final conversion's formula
             const int32_t t = A.track_slot ? A.track_slot[i] : -1;
             if (t >= 0) {
@@ -511,8 +522,8 @@ __global__ __launch_bounds__(kFinalizeThreads) void integrate_kernel(IntegrateAr
         if (n < last) {
             const StepCoef cf = A.coef[row];
             for (int c = 0; c < 3; ++c) {
-                p[c] += cf.k1 * g[c];
-                xx[c] += cf.d * p[c];
+                p[c] = fma(cf.k1, g[c], p[c]);
+                xx[c] = fma(cf.d, p[c], xx[c]);
                 if (A.box > 0.0)
                     xx[c] -= A.box * floor(xx[c] / A.box);
             }
