@@ -1515,13 +1515,13 @@ int run_impl(const RunParams &P, const Boxes &b)
     StepCoef *coef = static_cast<StepCoef *>(ws->coef.ptr);
     double *p = static_cast<double *>(ws->p.ptr);
     CHECK_HIP(launch_coefficients(P.H0, P.OmR, P.OmM, P.OmK, P.OmL, P.a_begin, P.a_end,
-                                  P.n_steps, P.first, P.last, 0, coef, s));
+                                  P.n_steps, P.first, P.last, 0, coef, s,
+                                  {step_counter(ws), work_counter(ws), done_counter(ws)}));
     if (wl.cfg.form == 4 && !diag && !g_opt.graph && !g_opt.timer && nsteps > 0 &&
         !overlap(P.v, 3 * P.N, P.x, 3 * P.N)) {
         CHECK_RC(prepare_tracks(ws, P));
         return enqueue_small_run(ws, P, wl, mask, nsteps);
     }
-    CHECK_RC(set_step(ws, P.first, P.first, P.last, s));
     CHECK_RC(run_forward_sweep(ws, wl, P.precision, diag, mask, P.x, P.m, P.N, s, false));
 
     IntegrateArgs A;

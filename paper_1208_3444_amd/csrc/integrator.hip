@@ -162,9 +162,16 @@ __device__ StepCoef step_coefficients(const Cosmo &c, double a_begin, double a_e
 __global__ __launch_bounds__(64) void coefficients_kernel(Cosmo c, double a_begin, double a_end,
                                                           int64_t n_steps, int64_t first,
                                                           int64_t last, int half_time,
-                                                          StepCoef *coef)
+                                                          StepCoef *coef, RunStart run)
 {
     __shared__ CoefShared sh[4];
+    if (run.step && blockIdx.x == 0 && threadIdx.x == 0) {
+        run.step[0] = first;
+        run.step[1] = first;
+        run.step[2] = last;
+        *run.work_counter = 0;
+        *run.done_counter = 0;
+    }
     const int grp = (int)threadIdx.x >> 4, l = (int)threadIdx.x & 15;
     const int64_t n = first + 4 * (int64_t)blockIdx.x + grp;
     if (n >= last)
@@ -1014,12 +1021,13 @@ __global__ void ftle_kernel(const double *__restrict__ grad, const int64_t *__re
 
 hipError_t launch_coefficients(double H0, double OmR, double OmM, double OmK, double OmL,
                                double a_begin, double a_end, int64_t n_steps, int64_t first,
-                               int64_t last, int half_time, StepCoef *coef, hipStream_t stream)
+                               int64_t last, int half_time, StepCoef *coef, hipStream_t stream,
+                               const RunStart &run)
 {
     Cosmo c{H0, OmR, OmM, OmK, OmL};
     const int64_t n = last - first;
     hipLaunchKernelGGL(coefficients_kernel, dim3(blocks_for(n, 4)), dim3(64), 0, stream, c,
-                       a_begin, a_end, n_steps, first, last, half_time, coef);
+                       a_begin, a_end, n_steps, first, last, half_time, coef, run);
     return hipGetLastError();
 }
 
