@@ -415,7 +415,11 @@ int colatus_forces_noalloc(const double *x, const double *m, int64_t N, double e
  *   lambda_t: DEVICE [n_tracers], written; lambda_lna, blocks: DEVICE
  *   [n_tracers] and [n_tracers][3][3], or NULL.
  * Other arguments, precision, checkpointing and the external terms as in
- * colatus_adjoint.  1 <= n_tracers <= 1365 and every index in [0, N), else
+ * colatus_adjoint.  With FP64 pairs and enough tracers (at least two in small
+ * boxes, five in large ones) the transpose-Jacobian sums run as matrix
+ * products, in another order of the same FP64 operations; the sums of a
+ * caller's cotangents (colatus_adjoint, colatus_force_vjp) never do.
+ * 1 <= n_tracers <= 1365 and every index in [0, N), else
  * COLATUS_EINVAL.  Device scratch: the adjoint's, with 3 n_tracers
  * cotangents (about 0.45 GB at N = 32768 and 64 tracers).                  */
 int colatus_ftle(const double *x0, const double *v0, const double *m, int64_t N,

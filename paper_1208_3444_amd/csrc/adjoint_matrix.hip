@@ -1,5 +1,6 @@
 // Transpose-Jacobian pair sum of many cotangents on the FP64 matrix
-// instruction (form 3 of the adjoint, FP64 pairs).  With M(d) = r^-3 I -
+// instruction (form 3 of the adjoint, FP64 pairs, the unit cotangents of
+// colatus_ftle: matrix_adjoint in api.cpp says why only those).  With M(d) = r^-3 I -
 // 3 r^-5 d d^T,
 //   out_k = sum_j M(d)(m_k lam_j - m_j lam_k) = m_k P_k - D_k lam_k,
 //   P_k = sum_j M(d_kj) lam_j,   D_k = sum_j m_j M(d_kj),

@@ -534,15 +534,25 @@ TileCfg small_form_cfg(int precision)
     return TileCfg{precision == COLATUS_FP64 ? kSmallT64 : kSmallT32, kSmallTile, 1, 4};
 }
 
-// The adjoint's matrix form (adjoint_matrix.hip), FP64 pairs: its products hold
-// 16 cotangents, up to three times over, at 1607 / 2240 / 3110 us (two steps
-// at N = 8000), where the ordered loop takes 350-390 for four cotangents and
-// 235 for each one left over.  Ordered / matrix there and at N = 32768: 12
-// cotangents 1540 / 1631 and 20930 / 23360; 13, 1777 / 1633 and 24200 / 23400;
-// 16, 1892 / 1647 and 26460 / 23680; 17, 2156 / 2246 and 31570 / 32680; 18, 2392
-// / 2244 and 34680 / 32660; 49, 5633 / 4531 and 85600 / 68700.  A few boxes
+// The adjoint's matrix form (adjoint_matrix.hip), FP64 pairs, for the unit cotangents
+// of colatus_ftle alone.  It takes m_k sum_j M lam_j - (sum_j m_j M) lam_k from two
+// sums, so where lam / m varies little between close particles it loses what the
+// other loops keep by forming m_k lam_j - m_j lam_k pair by pair: equal masses, a
+// clumped cloud, lam = 1 + 1e-3 x, relative error 3e-11 against 3e-15 (and a
+// uniform lam gives rounding noise in place of 0).  Cotangents that a caller
+// hands over may be such; those that start on one particle are not: their own
+// products within 0.6 to 1.5 times the other loops' error over 500 to 8000
+// particles, the exponents' blocks with the same error.
+// Its products hold 16 cotangents, up to three times over, at 1607 / 2240 / 3110 us
+// (two steps at N = 8000), where the ordered loop takes 350-390 for four
+// cotangents and 235 for each one left over.  Ordered / matrix there and at
+// N = 32768: 12 cotangents 1540 / 1631 and 20930 / 23360; 13, 1777 / 1633 and 24200
+// / 23400; 16, 1892 / 1647 and 26460 / 23680; 17, 2156 / 2246 and 31570 / 32680; 18,
+// 2392 / 2244 and 34680 / 32660; 49, 5633 / 4531 and 85600 / 68700.  A few boxes
 // leave the ordered loop waiting on each launch: 6 cotangents 445 / 179 at
-// N = 500, 521 / 346 at 3000, but 528 / 511 at 4000 and 8 there 402 / 514.
+// N = 500, 521 / 346 at 3000, but 528 / 511 at 4000 and 8 there 402 / 514.  Batches
+// (three steps): 2000 boxes of 10, 48 cotangents 1934 / 846; 200 of 30, 15
+// cotangents 425 / 159.
 constexpr int kMatrixSmallBlocks = 48;  // blocks of 64 targets
 
 bool matrix_adjoint(const Boxes &b, int n_cot)
@@ -552,8 +562,6 @@ bool matrix_adjoint(const Boxes &b, int n_cot)
     return n_cot >= 13 && n_cot != 17;
 }
 
-// Items of 64 targets; as few source slices as fill whole rounds of two blocks
-// per CU to 95 % (or the best of sixteen).
 TileCfg matrix_cfg(const Boxes &b, int n_cu)
 {
     const int tb = n_target_blocks(b, 64);
@@ -581,8 +589,6 @@ TileCfg matrix_cfg(const Boxes &b, int n_cu)
 // both unless the boxes are too small to fill the GPU with its items.
 TileCfg heuristic_cfg(const Boxes &b, int precision, int kind, int n_cu, int n_cot = 1)
 {
-    if (kind == 1 && precision == COLATUS_FP64 && matrix_adjoint(b, n_cot))
-        return matrix_cfg(b, n_cu);
     if (symmetric_waves(b) < kSmallSymWaves)
         return kind == 0 && small_form(b, precision, n_cu) ? small_form_cfg(precision)
                                           : small_boxes_cfg(b, kind);
@@ -625,7 +631,7 @@ TileCfg apply_overrides(TileCfg c, int kind, int precision, const Boxes &b, int 
         if (want == 2) {
             c = kind == 0 ? grouped_cfg(b) : symmetric_cfg(b, 4, 64);
         } else {
-            if (c.form >= 2)
+            if (c.form == 2)
                 c = ordered_cfg(b, precision, kind, n_cu);
             c.form = want;
         }
@@ -1165,8 +1171,10 @@ int prepare_box_mass(Workspace *ws, const WorkList &wl, const double *m, hipStre
 int slot_mode_of(const WorkList &wl, int precision) { return slot_mode_for(wl.cfg, precision); }
 
 // Choose (and if asked, autotune) the tile shape, then make the work list.
+// unit_cot: the adjoint's cotangents start as unit vectors (matrix_adjoint).
 int prepare_worklist(Workspace *ws, int kind, const Boxes &b, int64_t N, int precision,
-                     const double *x, const double *m, int n_cot, hipStream_t s)
+                     const double *x, const double *m, int n_cot, hipStream_t s,
+                     bool unit_cot = false)
 {
     const int n_cu = cu_count(ws->device);
     TuneKey key{pow2_ceil(b.max_n), (int)std::min<size_t>(pow2_ceil(b.eps.size()), 1 << 20),
@@ -1177,6 +1185,9 @@ int prepare_worklist(Workspace *ws, int kind, const Boxes &b, int64_t N, int pre
         cfg = it->second;
     } else {
         cfg = heuristic_cfg(b, precision, kind, n_cu, n_cot);
+        if (unit_cot && kind == 1 && precision == COLATUS_FP64 && g_opt.pair_form < 0 &&
+            matrix_adjoint(b, n_cot))
+            cfg = matrix_cfg(b, n_cu);
         if (g_opt.autotune && x && m) {
             // time candidates on the live data; scratch outputs only
             std::vector<TileCfg> cand;
@@ -1916,7 +1927,7 @@ int adjoint_impl(Workspace *ws, const AdjointParams &P, const Boxes &b)
     for (double e : b.eps)
         mask = mask || e == 0.0;
     CHECK_RC(prepare_worklist(ws, 0, b, N, precision, x0, m, 1, s));
-    CHECK_RC(prepare_worklist(ws, 1, b, N, precision, x0, m, n_cot, s));
+    CHECK_RC(prepare_worklist(ws, 1, b, N, precision, x0, m, n_cot, s, lam_xN == nullptr));
     const WorkList &wf = *ws->fwd;
     const WorkList &wa = *ws->adj;
     CHECK_RC(prepare_box_mass(ws, wf, m, s));
