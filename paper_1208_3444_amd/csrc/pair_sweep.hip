@@ -2559,14 +2559,17 @@ hipError_t launch_ewald_real(int precision, bool with_phi, const double *x, cons
 }
 
 // box_mass[b] = the common mass of box b, or NaN if its masses differ (or one
-// is not positive).  A block per box compares a box's masses with its first; a
-// box too large for that (kMassBlock) takes two passes over the whole grid:
-// every box takes its first mass, then every particle whose mass differs marks
-// the box NaN.  Those marks all store the same value, so the result does not
-// depend on their order.  One launch against two: a cached step of 5000
-// particles 36 -> 33 us, forces of 5000 24.3 -> 23.7, but of 8000 34.1 -> 34.3
-// and of 32000 179 -> 182 (one block's loads take longer than a launch).
+// is not positive).  A block per box compares a box's masses with its first;
+// boxes too large (kMassBlock) or too many (kMassBoxes) for that take two passes
+// over the whole grid: every box takes its first mass, then every particle whose
+// mass differs marks the box NaN.  Those marks all store the same value, so the
+// result does not depend on their order.  One launch against two: a cached step
+// of 5000 particles 36 -> 33 us, forces of 5000 24.3 -> 23.7, but of 8000 34.1 ->
+// 34.3 and of 32000 179 -> 182 (one block's loads take longer than a launch); the
+// kernels alone, 2000 boxes of 200 7.6 / 9.6 us, 10 000 boxes of 30 29 / 9.4,
+// 100 000 of 10 268 / 18 (a block of 1024 is mostly idle there).
 constexpr int64_t kMassBlock = 6144;
+constexpr int kMassBoxes = 2048;
 
 __global__ __launch_bounds__(1024) void box_mass_kernel(const double *__restrict__ m,
                                                         const int64_t *__restrict__ off,
@@ -2620,7 +2623,7 @@ hipError_t launch_box_mass(const double *m, const int64_t *box_offsets, int n_bo
 {
     if (n_boxes < 1 || N < 1)
         return hipErrorInvalidValue;
-    if (max_n <= kMassBlock) {
+    if (max_n <= kMassBlock && n_boxes <= kMassBoxes) {
         hipLaunchKernelGGL(box_mass_kernel, dim3((unsigned)n_boxes), dim3(1024), 0, stream, m,
                            box_offsets, box_mass);
         return hipGetLastError();
