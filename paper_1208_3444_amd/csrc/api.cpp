@@ -977,6 +977,9 @@ int upload_worklist(WorkList &wl, const Boxes &b, int64_t N, const TileCfg &cfg,
     wl.N = N;
     wl.eps = b.eps;
     wl.cfg = cfg;
+    wl.cfg.pairs = 0;
+    for (const WorkItem &w : wl.items)
+        wl.cfg.pairs += cfg.form == 2 && w.kind == 0;
     return COLATUS_OK;
 }
 
@@ -1240,7 +1243,7 @@ int prepare_worklist(Workspace *ws, int kind, const Boxes &b, int64_t N, int pre
                     CHECK_HIP(hipEventRecord(e0, s));
                     if (kind == 0)
                         CHECK_HIP(launch_pair_sweep(
-                            precision, c.form, c, false, false, x, m, N,
+                            precision, c.form, tmp.cfg, false, false, x, m, N,
                             static_cast<const WorkItem *>(tmp.d_items.ptr), (int)tmp.items.size(),
                             work_counter(ws), g_opt.persistent != 0,
                             static_cast<const double *>(ws->box_mass.ptr),
@@ -1374,7 +1377,8 @@ std::vector<uint64_t> step_graph_key(const Workspace *ws, const RunParams &P,
     k.add(A.ewald_g); k.add(A.ewald_p); k.add(A.box);
     // pair sweep
     k.add((int64_t)P.precision); k.add((int64_t)wl.cfg.R); k.add((int64_t)wl.cfg.tpb);
-    k.add((int64_t)wl.cfg.slices); k.add((int64_t)wl.cfg.form); k.add((int64_t)(P.diag != nullptr));
+    k.add((int64_t)wl.cfg.slices); k.add((int64_t)wl.cfg.form); k.add(wl.cfg.pairs);
+    k.add((int64_t)(P.diag != nullptr));
     k.add((int64_t)mask); k.add(P.x); k.add(P.m); k.add(P.N); k.add(wl.d_items.ptr);
     k.add((int64_t)wl.items.size()); k.add((int64_t)g_opt.persistent); k.add(ws->part.ptr);
     k.add(ws->part_phi.ptr); k.add(ws->counters.ptr);

@@ -128,6 +128,7 @@ struct TileCfg {
                    // per workgroup of four waves (pair_sweep_sym_grp_kernel),
                    // kOneSided = both sides of a pair as items of their own
                    // (the periodic real space of small boxes, FP32 pairs)
+    int64_t pairs = 0; // form 2, a work list's: its pairs of parts, over all boxes
 };
 constexpr int kOneSided = 2;
 

@@ -247,6 +247,7 @@ extern "C" int colatus_forces_noalloc(const double *x, const double *m, int64_t 
         return COLATUS_EHIP;
     TileCfg cfg{4, 64, P, 2};
     cfg.group = 1;
+    cfg.pairs = (int64_t)P * (P - 1) / 2;
     if (launch_pair_sweep(precision, cfg.form, cfg, phi != nullptr, eps == 0.0, x, m, N, items,
                           n_items, counter, false, box_mass, part, phi ? part_phi : nullptr,
                           nullptr, s) != hipSuccess)

@@ -417,15 +417,68 @@ template <> __device__ __forceinline__ double adj_pad<double>() { return 1e150; 
 // step uses them (the masses start one lane back, the reactions, zero at
 // first, take one more rotation at the end), so that all rotations share the
 // one burst.  A piece of a diagonal (R = 1, no reaction) takes U = 4 steps at
-// a time for the same batch of four.  The order of every sum is that of the
-// plain loop.  Measured (FP32, equal masses, one 64^3 evaluation / 20 steps
-// at 32^3): 13.0 / 4.66 ms with the compiler's own order, 10.3 / 3.63 ms so.
-template <typename T, int R, bool REACT, bool EQM, bool PHI, bool MASK>
+// a time for the same batch of four.  Measured (FP32, equal masses, one 64^3
+// evaluation / 20 steps at 32^3): 13.0 / 4.66 ms with the compiler's own order,
+// 10.3 / 3.63 ms so.  PHASED = false leaves the order to the compiler, for sweeps
+// with too few waves to pair (sym_phased); both give the same bits.
+template <typename T, int R, bool REACT, bool EQM, bool PHI, bool MASK, bool PHASED>
 __device__ __forceinline__ void sym_chunk(T sx, T sy, T sz, T sm, T &qx, T &qy, T &qz, T &qp,
                                           const T (&xi)[R], const T (&yi)[R], const T (&zi)[R],
                                           const T (&mi)[R], T eps2, T (&ax)[R], T (&ay)[R],
                                           T (&az)[R], T (&ap)[R])
 {
+    if constexpr (!PHASED) {
+#pragma unroll 2
+        for (int k = 0; k < 64; ++k) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const T dx = sx - xi[r];
+                const T dy = sy - yi[r];
+                const T dz = sz - zi[r];
+                T s = fma_t(dx, dx, eps2);
+                s = fma_t(dy, dy, s);
+                s = fma_t(dz, dz, s);
+                T rinv, w;
+                if constexpr (sizeof(T) == 8 && !PHI) {
+                    w = rinv3_from(s, rsq_raw(s));
+                    if constexpr (MASK)
+                        w = s > (T)0.0 ? w : (T)0.0;
+                } else {
+                    rinv = rsqrt_from(s, rsq_raw(s));
+                    if constexpr (MASK)
+                        rinv = s > (T)0.0 ? rinv : (T)0.0;
+                    w = rinv * (rinv * rinv);
+                }
+                const T wt = EQM ? w : sm * w;
+                ax[r] = fma_t(wt, dx, ax[r]);
+                ay[r] = fma_t(wt, dy, ay[r]);
+                az[r] = fma_t(wt, dz, az[r]);
+                if constexpr (PHI)
+                    ap[r] += EQM ? rinv : sm * rinv;
+                if constexpr (REACT) {
+                    const T ws = EQM ? w : mi[r] * w;
+                    qx = fma_t(-ws, dx, qx);
+                    qy = fma_t(-ws, dy, qy);
+                    qz = fma_t(-ws, dz, qz);
+                    if constexpr (PHI)
+                        qp += EQM ? rinv : mi[r] * rinv;
+                }
+            }
+            sx = wave_rotate(sx);
+            sy = wave_rotate(sy);
+            sz = wave_rotate(sz);
+            if constexpr (!EQM)
+                sm = wave_rotate(sm);
+            if constexpr (REACT) {
+                qx = wave_rotate(qx);
+                qy = wave_rotate(qy);
+                qz = wave_rotate(qz);
+                if constexpr (PHI)
+                    qp = wave_rotate(qp);
+            }
+        }
+        return;
+    }
     constexpr int U = R == 1 && !REACT ? 4 : 1;
     constexpr int B = U * R;
     static_assert(U == 1 || !REACT, "a reaction rotates every step");
@@ -605,11 +658,11 @@ __device__ __forceinline__ void sym_item(const WorkItem &w, const double *__rest
         }
         T qx = (T)0.0, qy = (T)0.0, qz = (T)0.0, qp = (T)0.0;
         if (eqm)
-            sym_chunk<T, R, REACT, true, PHI, MASK>(sx, sy, sz, sm, qx, qy, qz, qp, xi, yi, zi, mi,
-                                                 eps2, ax, ay, az, ap);
+            sym_chunk<T, R, REACT, true, PHI, MASK, true>(sx, sy, sz, sm, qx, qy, qz, qp, xi, yi, zi,
+                                                       mi, eps2, ax, ay, az, ap);
         else
-            sym_chunk<T, R, REACT, false, PHI, MASK>(sx, sy, sz, sm, qx, qy, qz, qp, xi, yi, zi, mi,
-                                                  eps2, ax, ay, az, ap);
+            sym_chunk<T, R, REACT, false, PHI, MASK, true>(sx, sy, sz, sm, qx, qy, qz, qp, xi, yi, zi,
+                                                        mi, eps2, ax, ay, az, ap);
         if constexpr (FOLD) {
             if ((c & 3) == 3 || c == n_chunks - 1) {
 #pragma unroll
@@ -876,7 +929,7 @@ __device__ __forceinline__ void grp_store(double *__restrict__ part, double *__r
 // targets' partial sums are left in (ax, ay, az, ap); the reactions go to
 // rst[NQ][256] (LDS, chunk c at 64 c + lane) when the item has a reaction
 // partner, else straight to slot rslice.
-template <typename T, int R, bool REACT, bool PHI, bool MASK>
+template <typename T, int R, bool REACT, bool PHI, bool MASK, bool PHASED>
 __device__ __forceinline__ void grp_item(const WorkItem &w, const double *__restrict__ X,
                                          const double *__restrict__ Y,
                                          const double *__restrict__ Z,
@@ -929,11 +982,11 @@ __device__ __forceinline__ void grp_item(const WorkItem &w, const double *__rest
         }
         T qx = (T)0.0, qy = (T)0.0, qz = (T)0.0, qp = (T)0.0;
         if (eqm)
-            sym_chunk<T, R, REACT, true, PHI, MASK>(sx, sy, sz, sm, qx, qy, qz, qp, xi, yi, zi, mi,
-                                                 eps2, ax, ay, az, ap);
+            sym_chunk<T, R, REACT, true, PHI, MASK, PHASED>(sx, sy, sz, sm, qx, qy, qz, qp, xi, yi, zi,
+                                                         mi, eps2, ax, ay, az, ap);
         else
-            sym_chunk<T, R, REACT, false, PHI, MASK>(sx, sy, sz, sm, qx, qy, qz, qp, xi, yi, zi,
-                                                  mi, eps2, ax, ay, az, ap);
+            sym_chunk<T, R, REACT, false, PHI, MASK, PHASED>(sx, sy, sz, sm, qx, qy, qz, qp, xi, yi, zi,
+                                                          mi, eps2, ax, ay, az, ap);
         if constexpr (REACT) {
             if (rst) {
                 rst[0][c * 64 + lane] = qx;
@@ -948,9 +1001,10 @@ __device__ __forceinline__ void grp_item(const WorkItem &w, const double *__rest
     }
 }
 
-template <typename T, bool PHI, bool MASK>
+// FP32 pairs: five waves share each SIMD (96 VGPRs), six with the plain loop (80).
+template <typename T, bool PHI, bool MASK, bool PHASED>
 __global__ __launch_bounds__(64 * kGroupWaves)
-__attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 5 : 3))) void
+__attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 3 : PHASED ? 5 : 6))) void
 pair_sweep_sym_grp_kernel(
     const double *__restrict__ x, const double *__restrict__ m, int64_t N,
     const WorkItem *__restrict__ items, int n_groups, int *__restrict__ counter,
@@ -980,9 +1034,9 @@ pair_sweep_sym_grp_kernel(
         T ax[4], ay[4], az[4], ap[4];
         bool valid[4] = {false, false, false, false};
         if (w.kind == 0) {
-            grp_item<T, 4, true, PHI, MASK>(w, X, Y, Z, m, N, mbox, part, part_phi,
-                                            w.rmate ? rbuf[wave] : nullptr, ax, ay, az, ap,
-                                            valid);
+            grp_item<T, 4, true, PHI, MASK, PHASED>(w, X, Y, Z, m, N, mbox, part, part_phi,
+                                                    w.rmate ? rbuf[wave] : nullptr, ax, ay, az,
+                                                    ap, valid);
             if (!w.tmate) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
@@ -1003,8 +1057,8 @@ pair_sweep_sym_grp_kernel(
         } else if (w.kind == 1) {
             T bx[1], by[1], bz[1], bp[1];
             bool v1[1];
-            grp_item<T, 1, false, PHI, MASK>(w, X, Y, Z, m, N, mbox, part, part_phi, nullptr, bx,
-                                             by, bz, bp, v1);
+            grp_item<T, 1, false, PHI, MASK, PHASED>(w, X, Y, Z, m, N, mbox, part, part_phi,
+                                                     nullptr, bx, by, bz, bp, v1);
             if (v1[0])
                 grp_store<T, PHI>(part, part_phi, N, (int64_t)w.slice, w.i0 + lane, bx[0], by[0],
                                   bz[0], bp[0], scale);
@@ -1632,12 +1686,33 @@ hipError_t dispatch_sym_flags(bool phi, bool mask, const FwdArgs &a)
                 : launch_sym<T, ACC, R, W, false, false>(a);
 }
 
-// Grouped symmetric sweep: a.items holds kGroupWaves items per group.
-template <typename T, bool PHI, bool MASK>
-hipError_t launch_sym_grp(const FwdArgs &a)
+// Whether a grouped sweep takes the phased loop (sym_chunk), which pays once most
+// SIMDs hold two waves to pair.  Plain / phased, us, equal masses unless said:
+// FP32: 10 000 particles (195 groups of part pairs, 1 per CU at most) 43.3 / 44.9,
+// 11 500 (259) 64.1 / 47.7, 40 boxes of 300-3300 (356 groups, of them fewer
+// than 256 of pairs) 44.8 / 46.1, 24 000 140 / 114.  FP64, its v_rsq alone to hide:
+// 10 000 (235 groups in all) 55.9 / 58.4, 11 000 (280) 61.5 / 60.3, 32 768 350 /
+// 344; with the potential 8000 61.9 / 67.6, 15 000 (501) 110 / 113, 16 000 (567)
+// 117 / 116, 49 boxes of 300-3300 (533) 80.2 / 77.5.  Boxes of one part, without
+// pairs: FP32 2000 boxes of 30 (500 groups) 10.8 / 10.4, 100 000 (25 000) 164 / 179
+// (unequal masses 191 / 184), with the potential 8000 boxes of 200 212 / 210; FP64
+// 2000 of 30 13.0 / 13.9, 8000 of 200 (8000) 328 / 320, with the potential 13.4 /
+// 15.5 and 309 / 327 (100 000 of 30).
+bool sym_phased(bool fp64, bool phi, int n_groups, const TileCfg &cfg)
 {
-    auto k = pair_sweep_sym_grp_kernel<T, PHI, MASK>;
-    const int n_groups = a.n_items / kGroupWaves;
+    constexpr int kCUs = 256;
+    if (cfg.slices == 1)
+        return fp64 ? !phi && n_groups >= 4 * kCUs : phi || n_groups < 4 * kCUs;
+    if (fp64)
+        return n_groups > (phi ? 2 * kCUs : kCUs);
+    return cfg.pairs > (int64_t)kGroupWaves * kCUs;
+}
+
+// Grouped symmetric sweep: a.items holds kGroupWaves items per group.
+template <typename T, bool PHI, bool MASK, bool PHASED>
+hipError_t launch_sym_grp(const FwdArgs &a, int n_groups)
+{
+    auto k = pair_sweep_sym_grp_kernel<T, PHI, MASK, PHASED>;
     const int tpb = 64 * kGroupWaves;
     int grid = a.persistent ? persistent_grid(k, tpb, 0, n_groups) : n_groups;
     if (grid <= 0)
@@ -1648,14 +1723,25 @@ hipError_t launch_sym_grp(const FwdArgs &a)
     return hipGetLastError();
 }
 
+template <typename T, bool PHASED>
+hipError_t dispatch_sym_grp_flags(bool phi, bool mask, const FwdArgs &a, int n_groups)
+{
+    if (phi)
+        return mask ? launch_sym_grp<T, true, true, PHASED>(a, n_groups)
+                    : launch_sym_grp<T, true, false, PHASED>(a, n_groups);
+    return mask ? launch_sym_grp<T, false, true, PHASED>(a, n_groups)
+                : launch_sym_grp<T, false, false, PHASED>(a, n_groups);
+}
+
 template <typename T>
-hipError_t dispatch_sym_grp(bool phi, bool mask, const FwdArgs &a)
+hipError_t dispatch_sym_grp(const TileCfg &cfg, bool phi, bool mask, const FwdArgs &a)
 {
     if (a.n_items % kGroupWaves != 0)
         return hipErrorInvalidValue;
-    if (phi)
-        return mask ? launch_sym_grp<T, true, true>(a) : launch_sym_grp<T, true, false>(a);
-    return mask ? launch_sym_grp<T, false, true>(a) : launch_sym_grp<T, false, false>(a);
+    const int n_groups = a.n_items / kGroupWaves;
+    return sym_phased(sizeof(T) == 8, phi, n_groups, cfg)
+               ? dispatch_sym_grp_flags<T, true>(phi, mask, a, n_groups)
+               : dispatch_sym_grp_flags<T, false>(phi, mask, a, n_groups);
 }
 
 template <typename T, int ACC>
@@ -1664,7 +1750,7 @@ hipError_t dispatch_sym(const TileCfg &cfg, bool phi, bool mask, const FwdArgs &
     if (cfg.group) {
         if (cfg.R != 4 || cfg.tpb != 64)
             return hipErrorInvalidValue;
-        return dispatch_sym_grp<T>(phi, mask, a);
+        return dispatch_sym_grp<T>(cfg, phi, mask, a);
     }
     if constexpr (sizeof(T) == 4) {
         if (cfg.R == 4 && cfg.tpb == 64)

@@ -1,0 +1,39 @@
+"""The grouped symmetric sweep picks its pair loop (phased or plain) by its number of
+groups and of pairs of parts; both loops give the same bits, so a box's field does
+not depend on what else is in the call."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1208_3444_amd import colatus, inputs
+from conftest import to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed_twosum", "fp32"])
+@pytest.mark.parametrize("equal", [True, False])
+@pytest.mark.parametrize("n,copies", [(30, 5000), (200, 1100), (700, 700), (5000, 12),
+                                      (11500, 2)])
+def test_a_box_alone_and_among_others(dev, n, copies, equal, prec):
+    """One box by itself (few groups) and in a batch of copies (many): eps 0 and
+    not, with the potential and without."""
+    x, m = inputs.random_cloud(n, n, scale=0.5)
+    m = np.full(n, 0.7 / n) if equal else m
+    off = np.arange(copies + 1) * n
+    xs, ms = (to_dev(np.tile(a, copies), dev) for a in (x, m))
+    x, m = to_dev(x, dev), to_dev(m, dev)
+    colatus.set_option(colatus.OPT_PAIR_FORM, 2)
+    try:
+        for eps in (0.0, 0.02):
+            many, phi = colatus.forces(xs, ms, 0.0, precision=prec, with_phi=True,
+                                       batch=(off, np.full(copies, eps)))
+            only = colatus.forces(xs, ms, 0.0, precision=prec, batch=(off, np.full(copies, eps)))
+            one, p1 = colatus.forces(x, m, eps, precision=prec, with_phi=True)
+            o1 = colatus.forces(x, m, eps, precision=prec)
+            for b in (0, copies - 1):
+                s = slice(off[b], off[b + 1])
+                assert torch.equal(many[:, s], one) and torch.equal(phi[s], p1)
+                assert torch.equal(only[:, s], o1)
+    finally:
+        colatus.set_option(colatus.OPT_PAIR_FORM, -1)
