@@ -1387,7 +1387,7 @@ __global__ __launch_bounds__(64) void adjoint_sweep_sym_kernel(
 // Pair loop of the adjoint sweep over one LDS tile.  With equal masses
 // (EQM) the bracket m_k lam_j - m_j lam_k is m (lam_j - lam_k); the common
 // m multiplies the slice's partial sum once instead.
-template <typename T, int R, int C, bool MASK, bool EQM, typename V>
+template <typename T, int R, int C, bool MASK, bool EQM, bool PHASED, typename V>
 __device__ __forceinline__ void adjoint_tile(const V *__restrict__ tile,
                                              const T *__restrict__ ltile, int nt,
                                              const T (&xi)[R], const T (&yi)[R],
@@ -1396,10 +1396,9 @@ __device__ __forceinline__ void adjoint_tile(const V *__restrict__ tile,
                                              T (&acc)[R][3 * C])
 {
     constexpr int LW = 3 * C;
-    // sources per batch: four FP32 pairs' estimates in one burst (FP64 instructions
-    // are never paired, and batching them measured 1 % slower)
-    constexpr int U = sizeof(T) == 4 ? 4 / R : 1;
-    const T minus3 = sizeof(T) == 4 ? in_vgpr((T)-3) : (T)-3;
+    // PHASED (FP32): four pairs' estimates in one burst, else the compiler's order
+    constexpr int U = PHASED ? 4 / R : 1;
+    const T minus3 = PHASED ? in_vgpr((T)-3) : (T)-3;
     for (int j0 = 0; j0 < nt; j0 += U) {
         T dx[U][R], dy[U][R], dz[U][R], s[U][R], y[U][R], mj[U];
 #pragma unroll
@@ -1417,14 +1416,14 @@ __device__ __forceinline__ void adjoint_tile(const V *__restrict__ tile,
                 s[u][r] = fma_t(dz[u][r], dz[u][r], s[u][r]);
             }
         }
-        if constexpr (sizeof(T) == 4)
+        if constexpr (PHASED)
             burst_begin();
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int r = 0; r < R; ++r)
                 y[u][r] = rsq_raw(s[u][r]);
-        if constexpr (sizeof(T) == 4)
+        if constexpr (PHASED)
             burst_end();
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -1469,7 +1468,7 @@ __device__ __forceinline__ void adjoint_tile(const V *__restrict__ tile,
     }
 }
 
-template <typename T, int ACC, int R, int TPB, int C, bool MASK>
+template <typename T, int ACC, int R, int TPB, int C, bool MASK, bool PHASED>
 __global__ __launch_bounds__(TPB) void adjoint_sweep_kernel(
     const double *__restrict__ x, const double *__restrict__ m, int64_t N,
     const double *__restrict__ lam, int n_cot, int c0,
@@ -1561,9 +1560,11 @@ __global__ __launch_bounds__(TPB) void adjoint_sweep_kernel(
             __syncthreads();
             const int nt = (int)((w.j1 - jt) < TPB ? (w.j1 - jt) : TPB);
             if (eqm)
-                adjoint_tile<T, R, C, MASK, true>(tile, ltile, nt, xi, yi, zi, mk, lk, eps2, acc);
+                adjoint_tile<T, R, C, MASK, true, PHASED>(tile, ltile, nt, xi, yi, zi, mk, lk, eps2,
+                                                          acc);
             else
-                adjoint_tile<T, R, C, MASK, false>(tile, ltile, nt, xi, yi, zi, mk, lk, eps2, acc);
+                adjoint_tile<T, R, C, MASK, false, PHASED>(tile, ltile, nt, xi, yi, zi, mk, lk,
+                                                           eps2, acc);
             if constexpr (ACC != kDirect) {
 #pragma unroll
                 for (int r = 0; r < R; ++r)
@@ -1814,23 +1815,46 @@ hipError_t dispatch_fwd_form(int form, const TileCfg &cfg, bool phi, bool mask, 
     return dispatch_fwd_shape<T, ACC, 0>(cfg, phi, mask, a);
 }
 
+// Whether the ordered adjoint sweep takes the phased loop (adjoint_tile; FP32 pairs):
+// up to one block of four waves per CU it hides latency, and eight cotangents always
+// gain.  Plain / phased, us, equal masses, N = 4096 (256 blocks), 6145 (625) and
+// 20 011: one cotangent 32.6 / 30.9, 39.2 / 42.0, 243 / 247; four 54.2 / 51.9, 80.0 /
+// 80.8, 512 / 519; eight 78.8 / 78.8, 153 / 151, 1031 / 1019.  Unequal masses gain
+// more (one cotangent 39.6 / 32.4, 44.7 / 43.9, 270 / 266), but a kernel with each
+// loop for its masses runs the plain one slower (N = 4097: 31.6 -> 34.0).  FP64
+// instructions are never paired, and batching them measured 1 % slower.
+template <typename T, int C> bool adj_phased(int n_items)
+{
+    return sizeof(T) == 4 && (C == 8 || n_items <= 256);
+}
+
+template <typename T, int ACC, int R, int TPB, int C, bool MASK, bool PHASED>
+hipError_t launch_adj_k(const double *x, const double *m, int64_t N, const double *lam, int n_cot,
+                        int c0, const WorkItem *items, int n_items, int *counter, bool persistent,
+                        const double *box_mass, double *part, hipStream_t stream)
+{
+    auto k = adjoint_sweep_kernel<T, ACC, R, TPB, C, MASK, PHASED>;
+    const int grid = persistent ? persistent_grid(k, TPB, 0, n_items) : n_items;
+    hipLaunchKernelGGL(k, dim3(grid), dim3(TPB), 0, stream, x, m, N, lam, n_cot, c0, items,
+                       n_items, counter, persistent ? 1 : 0, box_mass, part);
+    return hipGetLastError();
+}
+
 template <typename T, int ACC, int R, int TPB, int C>
 hipError_t launch_adj(bool mask, const double *x, const double *m, int64_t N, const double *lam,
                       int n_cot, int c0, const WorkItem *items, int n_items, int *counter,
                       bool persistent, const double *box_mass, double *part, hipStream_t stream)
 {
-    if (mask) {
-        auto k = adjoint_sweep_kernel<T, ACC, R, TPB, C, true>;
-        int grid = persistent ? persistent_grid(k, TPB, 0, n_items) : n_items;
-        hipLaunchKernelGGL(k, dim3(grid), dim3(TPB), 0, stream, x, m, N, lam, n_cot, c0, items,
-                           n_items, counter, persistent ? 1 : 0, box_mass, part);
-    } else {
-        auto k = adjoint_sweep_kernel<T, ACC, R, TPB, C, false>;
-        int grid = persistent ? persistent_grid(k, TPB, 0, n_items) : n_items;
-        hipLaunchKernelGGL(k, dim3(grid), dim3(TPB), 0, stream, x, m, N, lam, n_cot, c0, items,
-                           n_items, counter, persistent ? 1 : 0, box_mass, part);
-    }
-    return hipGetLastError();
+    auto go = [&](auto launch) {
+        return launch(x, m, N, lam, n_cot, c0, items, n_items, counter, persistent, box_mass, part,
+                      stream);
+    };
+    if constexpr (sizeof(T) == 4)
+        if (adj_phased<T, C>(n_items))
+            return mask ? go(launch_adj_k<T, ACC, R, TPB, C, true, true>)
+                        : go(launch_adj_k<T, ACC, R, TPB, C, false, true>);
+    return mask ? go(launch_adj_k<T, ACC, R, TPB, C, true, false>)
+                : go(launch_adj_k<T, ACC, R, TPB, C, false, false>);
 }
 
 template <typename T, int R, bool MASK>

@@ -37,3 +37,35 @@ def test_a_box_alone_and_among_others(dev, n, copies, equal, prec):
                 assert torch.equal(only[:, s], o1)
     finally:
         colatus.set_option(colatus.OPT_PAIR_FORM, -1)
+
+
+@pytest.mark.parametrize("prec", ["mixed_twosum", "mixed_f64acc", "fp32"])
+@pytest.mark.parametrize("equal", [True, False])
+@pytest.mark.parametrize("C", [1, 4, 8])
+def test_adjoint_of_a_box_alone_and_among_others(dev, C, equal, prec):
+    """The ordered adjoint loop: 4096 particles (256 blocks) by themselves and 16
+    boxes (4096 blocks).  The static step is so short that the positions stay as
+    they are, whatever the forward sweep's shape; the cotangents on the velocities
+    alone reach the positions' gradients through two transpose products."""
+    n, copies, dt = 4096, 16, 1e-18
+    x, m = inputs.random_cloud(n, n, scale=0.5)
+    m = np.full(n, 0.7 / n) if equal else m
+    lam = 1e9 * np.random.default_rng(C).standard_normal((C, 3, n))
+    off = np.arange(copies + 1) * n
+    static = dict(inputs.LCDM, H0=0.0)
+
+    def grads(k):
+        t = [to_dev(np.tile(a, k), dev) for a in (x, 0.0 * x, m, 0.0 * lam, lam)]
+        gx, _ = colatus.adjoint(*t[:3], 0.0, 1.0, static, 1.0, dt, 1, *t[3:], precision=prec,
+                                batch=(off[:k + 1], np.full(k, 0.01)))
+        return gx
+
+    colatus.set_option(colatus.OPT_PAIR_FORM, 0)
+    colatus.set_option(colatus.OPT_TILE_SLICES, 16)
+    try:
+        one, many = grads(1), grads(copies)
+    finally:
+        colatus.set_option(colatus.OPT_PAIR_FORM, -1)
+        colatus.set_option(colatus.OPT_TILE_SLICES, 0)
+    assert float(one.abs().max()) > 1e-10
+    assert torch.equal(one, many[..., :n]) and torch.equal(one, many[..., -n:])
