@@ -441,6 +441,8 @@ __device__ __forceinline__ void slot_sum(const double *part, int mode, int64_t o
         out[c] *= f;
 }
 
+// FROM_V: the run's first launch takes p from v, its last makes v from p.
+template <bool FROM_V>
 __global__ __launch_bounds__(kFinalizeThreads) void integrate_kernel(IntegrateArgs A)
 {
     __shared__ double shs[4][kSliceGroups][kIntBlock];
@@ -478,7 +480,7 @@ __global__ __launch_bounds__(kFinalizeThreads) void integrate_kernel(IntegrateAr
         }
         double g[3] = {A.G * gs[0], A.G * gs[1], A.G * gs[2]};
         double p[3] = {0.0, 0.0, 0.0};
-        if (A.v && n == first) {  // p = a^2 v, the conversion kernel's product
+        if (FROM_V && n == first) {  // p = a^2 v, the conversion kernel's product
             const double a0 = A.coef[0].a0;
             for (int c = 0; c < 3; ++c)
                 p[c] = a0 * a0 * A.v[c * N + i];
@@ -493,7 +495,7 @@ __global__ __launch_bounds__(kFinalizeThreads) void integrate_kernel(IntegrateAr
             const StepCoef cp = A.coef[row - 1];
             for (int c = 0; c < 3; ++c)
                 p[c] = fma(cp.k2, g[c], p[c]);
-            if (A.v && n == last)
+            if (FROM_V && n == last)
                 for (int c = 0; c < 3; ++c)
                     A.v[c * N + i] = p[c] / (cp.a1 * cp.a1);
             // tracer row at a_n: v = p / a^2, the final conversion's formula
@@ -623,7 +625,10 @@ __global__ void diag_prefix_kernel(int rows, int n_boxes, const StepCoef *__rest
     }
 }
 
-// acc = scale * sum_s part[s];  phi = -G (sum_s part_phi[s] - self term).
+// acc = scale * sum_s part[s];  phi = -G (sum_s part_phi[s] - self term).  EWALD:
+// periodic boundaries (see launch_forces_finalize).  A kernel of its own: with the
+// choice inside, the open box's took 12 us for 10 000 blocks instead of 11.
+template <bool EWALD>
 __global__ __launch_bounds__(kFinalizeThreads) void forces_finalize_kernel(
     int precision, const double *__restrict__ box_mass, const IntBlock *__restrict__ blocks,
     const double *__restrict__ part, const double *__restrict__ part_phi, int slot_mode,
@@ -646,7 +651,7 @@ __global__ __launch_bounds__(kFinalizeThreads) void forces_finalize_kernel(
         phe = ext_pull(ext, x[i], x[N + i], x[2 * N + i], blk.eps, f);
     if (lead && valid)
         for (int c = 0; c < 3; ++c) {
-            if (ewald_g)
+            if constexpr (EWALD)
                 g[c] += ewald_g[(int64_t)c * N + i];
             const double gc = scale * g[c] + inv_a3 * f[c];
             acc[(int64_t)c * N + i] = gc;
@@ -663,7 +668,7 @@ __global__ __launch_bounds__(kFinalizeThreads) void forces_finalize_kernel(
         double t[1];
         slot_sum<1>(part_phi, slot_mode, i, blk.n_slices, N, N, valid, shs, mbox, t);
         if (lead && valid) {
-            if (ewald_p)
+            if constexpr (EWALD)
                 t[0] += ewald_p[i];
             phi[i] = -G * (t[0] - self_potential(precision, m[i], blk.eps, mbox)) + phe;
         }
@@ -1041,8 +1046,8 @@ hipError_t launch_convert(int mode, const double *src, double *dst, int64_t N,
 
 hipError_t launch_integrate(const IntegrateArgs &args, hipStream_t stream)
 {
-    hipLaunchKernelGGL(integrate_kernel, dim3(args.n_blocks), dim3(kFinalizeThreads), 0, stream,
-                       args);
+    auto k = args.v ? integrate_kernel<true> : integrate_kernel<false>;
+    hipLaunchKernelGGL(k, dim3(args.n_blocks), dim3(kFinalizeThreads), 0, stream, args);
     return hipGetLastError();
 }
 
@@ -1076,9 +1081,9 @@ hipError_t launch_forces_finalize(int precision, const double *box_mass, const I
                                   const double *kick_p, double *kick_v, const StepCoef *kick_coef,
                                   const double *ewald_g, const double *ewald_p)
 {
-    hipLaunchKernelGGL(forces_finalize_kernel, dim3(n_blocks), dim3(kFinalizeThreads), 0, stream,
-                       precision, box_mass, blocks, part, part_phi, slot_mode, x, m, N, G, scale,
-                       ext, inv_a3, acc, phi, kick_p, kick_v, kick_coef, ewald_g, ewald_p);
+    auto k = ewald_g ? forces_finalize_kernel<true> : forces_finalize_kernel<false>;
+    hipLaunchKernelGGL(k, dim3(n_blocks), dim3(kFinalizeThreads), 0, stream, precision, box_mass,
+                       blocks, part, part_phi, slot_mode, x, m, N, G, scale, ext, inv_a3, acc, phi, kick_p, kick_v, kick_coef, ewald_g, ewald_p);
     return hipGetLastError();
 }
 

@@ -4,7 +4,7 @@ unequal masses mixed."""
 import numpy as np
 import pytest
 
-from paper_1208_3444_amd import colatus
+from paper_1208_3444_amd import colatus, inputs
 from conftest import to_dev
 
 pytestmark = pytest.mark.gpu
@@ -33,3 +33,30 @@ def test_masses_of_many_boxes(dev, n_boxes, prec, tol):
         mag = (np.abs(w) * np.sqrt((d ** 2).sum(0))).sum(1)
         err = np.linalg.norm(got[:, s] - (w * d).sum(2), axis=0)
         assert (err <= tol * mag + 1e-140).all(), b
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed_twosum"])
+@pytest.mark.parametrize("diag", [False, True])
+def test_runs_of_many_boxes(dev, prec, diag):
+    """The momentum made from the velocity by the integrations themselves (2048
+    blocks at most) and by conversions of their own: the same bits."""
+    n_boxes, n, few = 2050, 3, 40
+    rng = np.random.default_rng(4)
+    x, v = rng.uniform(size=(3, n_boxes * n)), 0.1 * rng.normal(size=(3, n_boxes * n))
+    m, off = np.full(n_boxes * n, 0.3), np.arange(n_boxes + 1) * n
+
+    def run(k):
+        t = [to_dev(np.ascontiguousarray(a[..., :k * n]), dev) for a in (x, v, m)]
+        rows = colatus.run(*t, 0.0, 1.0, inputs.LCDM, 0.2, 1.0, 9, first_step=2, last_step=5,
+                           precision=prec, batch=(off[:k + 1], np.full(k, 0.05)), diag=diag)
+        return t[0].cpu().numpy(), t[1].cpu().numpy(), rows
+
+    colatus.set_option(colatus.OPT_PAIR_FORM, 2)
+    try:
+        a, b = run(few), run(n_boxes)
+    finally:
+        colatus.set_option(colatus.OPT_PAIR_FORM, -1)
+    assert np.array_equal(a[0], b[0][:, :few * n]) and np.array_equal(a[1], b[1][:, :few * n])
+    if diag:
+        for r, q in zip(a[2], b[2]):
+            assert all(np.array_equal(r[f], q[f]) for f in colatus.DIAG_FIELDS)
