@@ -1537,12 +1537,14 @@ int run_impl(const RunParams &P, const Boxes &b)
     CHECK_HIP(launch_coefficients(P.H0, P.OmR, P.OmM, P.OmK, P.OmL, P.a_begin, P.a_end,
                                   P.n_steps, P.first, P.last, 0, coef, s,
                                   {step_counter(ws), work_counter(ws), done_counter(ws)}));
-    if (wl.cfg.form == 4 && !diag && !g_opt.graph && !g_opt.timer && nsteps > 0 &&
-        !overlap(P.v, 3 * P.N, P.x, 3 * P.N)) {
+    // arrays that share memory: only kernels that read nothing they still write
+    const bool apart = !overlap(P.v, 3 * P.N, P.x, 3 * P.N) && !overlap(P.v, 3 * P.N, P.m, P.N) &&
+                       !overlap(P.x, 3 * P.N, P.m, P.N);
+    if (wl.cfg.form == 4 && !diag && !g_opt.graph && !g_opt.timer && nsteps > 0 && apart) {
         CHECK_RC(prepare_tracks(ws, P));
         return enqueue_small_run(ws, P, wl, mask, nsteps);
     }
-    const bool from_v = (int)wl.blocks.size() <= kFromVBlocks;
+    const bool from_v = apart && (int)wl.blocks.size() <= kFromVBlocks;
     if (!from_v)
         CHECK_HIP(launch_convert(0, P.v, p, P.N, coef, 0, s));
     CHECK_RC(run_forward_sweep(ws, wl, P.precision, diag, mask, P.x, P.m, P.N, s, false));
@@ -2019,7 +2021,8 @@ int adjoint_impl(Workspace *ws, const AdjointParams &P, const Boxes &b)
 
     // ---- forward with checkpoints --------------------------------------
     CHECK_HIP(hipMemcpyAsync(xw, x0, n3 * sizeof(double), hipMemcpyDeviceToDevice, s));
-    if (keep_all && wf.cfg.form == 4 && !g_opt.timer) {
+    if (keep_all && wf.cfg.form == 4 && !g_opt.timer && !overlap(xN, 3 * N, m, N) &&
+        !overlap(vN, 3 * N, m, N)) {
         // small boxes: a step per launch, from slot n to slot n + 1
         SmallArgs S = small_run_args(ws, wf, precision, m, N, G, ext, n_steps);
         S.v = const_cast<double *>(v0);  // read by row 0 alone
