@@ -1696,7 +1696,7 @@ int ewald_plan(double L, int kind, EwaldPlanHost &P)
     for (int n2 = 1; n2 <= nmax * nmax; ++n2) {
         const double k2 = 4.0 * M_PI * M_PI * n2 / (L * L);
         const double window =
-            kind == 0 ? ewald_window().weight(n2) : std::exp(-k2 / (4.0 * P.alpha * P.alpha));
+            kind == 0 ? ewald_window().weight[n2] : std::exp(-k2 / (4.0 * P.alpha * P.alpha));
         wk[(size_t)n2] = 4.0 * M_PI / (L * L * L) * window / k2;
     }
     struct Col {

@@ -24,7 +24,7 @@
 //   force      (Phi - r phi) / r^3 = r_c^{-3} sum_i force[i] t^i
 // the potential's interpolated at Chebyshev nodes (degree 29), the force's its
 // derivative, 4 d/dt (degree 28); both within 1e-16 of the value at r_c.  All in
-// long double, once per process (0.7 ms).
+// long double, once per process (1 ms).
 #pragma once
 
 #include <cmath>
@@ -41,6 +41,9 @@ struct EwaldWindow {
     double force[kWindowDegree + 1], pot[kWindowDegree + 2];
     double self;       // lim_{r->0} r_c Phi / r = psi(0) / integral
     double mean_s2;    // int_0^1 s^2 psi / integral
+    // weight of reciprocal vector n by |n|^2 (a plan of a new box side needs them
+    // all: 0.3 of its 0.5 ms when they are evaluated anew)
+    double weight[kWindowN * kWindowN + 1];
 
     // P_0 .. P_{2 kTerms} at x
     static void legendre(long double x, long double *P)
@@ -67,12 +70,6 @@ struct EwaldWindow {
             s += b[i] * (P[2 * i + 1] - P[2 * i - 1]) / (4 * i + 1);
         return s + b[0] * x;
     }
-    // weight of reciprocal vector n, |n|^2 = n2 <= kWindowN^2
-    double weight(int n2) const
-    {
-        return (double)(psi(sqrtl((long double)n2) / kWindowN) / psi(0.0L));
-    }
-
     EwaldWindow()
     {
         const long double pi = acosl(-1.0L), c = pi * kWindowN;
@@ -106,7 +103,10 @@ struct EwaldWindow {
         for (int i = 0; i < kTerms; ++i)
             b[i] = v[i] * sqrtl((4 * i + 1) / 2.0L);
         integral = primitive(1.0L);
-        self = (double)(psi(0.0L) / integral);
+        const long double psi0 = psi(0.0L);
+        for (int n2 = 0; n2 <= kWindowN * kWindowN; ++n2)
+            weight[n2] = (double)(psi(sqrtl((long double)n2) / kWindowN) / psi0);
+        self = (double)(psi0 / integral);
         // x^2 = (2 P_2 + P_0) / 3 and int_0^1 P_n^2 = 1 / (2n + 1)
         mean_s2 = (double)((b[0] / 3.0L + 2.0L / 15.0L * b[1]) / integral);
         constexpr int n = kWindowDegree + 2;
