@@ -529,6 +529,13 @@ bool small_form(const Boxes &b, int precision, int n_cu)
     return b.max_n <= kSmallTiles * kSmallTile && n_target_blocks(b, kSmallT32) <= n_cu;
 }
 
+// Where the form only writes sums (diagnostics, Eqs. (3)-(5), checkpoints), the sweep's
+// own launch is not saved, and FP32 pairs of boxes up to this size take the ordered
+// loop (the same bits): ten steps of Eqs. (3)-(5), ordered / small, us, 64 particles
+// 96 / 106, 1000 137 / 141, 2000 137 / 140, 4096 170 / 166; with diagnostics 64 200 /
+// 212, 4096 314 / 290.  FP64 1000 150 / 103.
+constexpr int64_t kSmallSums32 = 2048;
+
 TileCfg small_form_cfg(int precision)
 {
     return TileCfg{precision == COLATUS_FP64 ? kSmallT64 : kSmallT32, kSmallTile, 1, 4};
@@ -1175,9 +1182,10 @@ int slot_mode_of(const WorkList &wl, int precision) { return slot_mode_for(wl.cf
 
 // Choose (and if asked, autotune) the tile shape, then make the work list.
 // unit_cot: the adjoint's cotangents start as unit vectors (matrix_adjoint).
+// sums: the forward sweeps write their sums for launches of their own to finish.
 int prepare_worklist(Workspace *ws, int kind, const Boxes &b, int64_t N, int precision,
                      const double *x, const double *m, int n_cot, hipStream_t s,
-                     bool unit_cot = false)
+                     bool unit_cot = false, bool sums = false)
 {
     const int n_cu = cu_count(ws->device);
     TuneKey key{pow2_ceil(b.max_n), (int)std::min<size_t>(pow2_ceil(b.eps.size()), 1 << 20),
@@ -1191,6 +1199,8 @@ int prepare_worklist(Workspace *ws, int kind, const Boxes &b, int64_t N, int pre
         if (unit_cot && kind == 1 && precision == COLATUS_FP64 && g_opt.pair_form < 0 &&
             matrix_adjoint(b, n_cot))
             cfg = matrix_cfg(b, n_cu);
+        if (cfg.form == 4 && sums && precision != COLATUS_FP64 && b.max_n <= kSmallSums32)
+            cfg = small_boxes_cfg(b, 0);
         if (g_opt.autotune && x && m) {
             // time candidates on the live data; scratch outputs only
             std::vector<TileCfg> cand;
@@ -1512,7 +1522,13 @@ int run_impl(const RunParams &P, const Boxes &b)
     std::lock_guard<std::mutex> lock(g_mu);
     CHECK_RC(get_workspace(P.stream, ws));
     hipStream_t s = P.stream;
-    CHECK_RC(prepare_worklist(ws, 0, b, P.N, P.precision, P.x, P.m, 1, s));
+    const bool diag = P.diag != nullptr;
+    // arrays that share memory: only kernels that read nothing they still write
+    const bool apart = !overlap(P.v, 3 * P.N, P.x, 3 * P.N) && !overlap(P.v, 3 * P.N, P.m, P.N) &&
+                       !overlap(P.x, 3 * P.N, P.m, P.N);
+    // steps of small boxes in one launch each
+    const bool whole = apart && !diag && !g_opt.graph && !g_opt.timer;
+    CHECK_RC(prepare_worklist(ws, 0, b, P.N, P.precision, P.x, P.m, 1, s, false, !whole));
     const WorkList &wl = *ws->fwd;
     CHECK_RC(prepare_box_mass(ws, wl, P.m, s));
     const int64_t nsteps = P.last - P.first;
@@ -1522,7 +1538,6 @@ int run_impl(const RunParams &P, const Boxes &b)
     CHECK_RC(ensure(ws->coef, (size_t)nsteps * sizeof(StepCoef)));
     CHECK_RC(ensure(ws->p, n3 * sizeof(double)));
     CHECK_RC(ensure(ws->part, (size_t)wl.max_slices * n3 * sizeof(double)));
-    const bool diag = P.diag != nullptr;
     if (diag) {
         CHECK_RC(ensure(ws->part_phi, (size_t)wl.max_slices * P.N * sizeof(double)));
         CHECK_RC(ensure(ws->diag_part, (size_t)rows * wl.blocks.size() * kDiagW * sizeof(double)));
@@ -1537,10 +1552,7 @@ int run_impl(const RunParams &P, const Boxes &b)
     CHECK_HIP(launch_coefficients(P.H0, P.OmR, P.OmM, P.OmK, P.OmL, P.a_begin, P.a_end,
                                   P.n_steps, P.first, P.last, 0, coef, s,
                                   {step_counter(ws), work_counter(ws), done_counter(ws)}));
-    // arrays that share memory: only kernels that read nothing they still write
-    const bool apart = !overlap(P.v, 3 * P.N, P.x, 3 * P.N) && !overlap(P.v, 3 * P.N, P.m, P.N) &&
-                       !overlap(P.x, 3 * P.N, P.m, P.N);
-    if (wl.cfg.form == 4 && !diag && !g_opt.graph && !g_opt.timer && nsteps > 0 && apart) {
+    if (wl.cfg.form == 4 && whole && nsteps > 0) {
         CHECK_RC(prepare_tracks(ws, P));
         return enqueue_small_run(ws, P, wl, mask, nsteps);
     }
@@ -1942,11 +1954,6 @@ int adjoint_impl(Workspace *ws, const AdjointParams &P, const Boxes &b)
     bool mask = false;
     for (double e : b.eps)
         mask = mask || e == 0.0;
-    CHECK_RC(prepare_worklist(ws, 0, b, N, precision, x0, m, 1, s));
-    CHECK_RC(prepare_worklist(ws, 1, b, N, precision, x0, m, n_cot, s, lam_xN == nullptr));
-    const WorkList &wf = *ws->fwd;
-    const WorkList &wa = *ws->adj;
-    CHECK_RC(prepare_box_mass(ws, wf, m, s));
     const size_t n3 = 3 * (size_t)N;
     if (checkpoint_every < 0) {
         // automatic: every position when they take at most a quarter of the
@@ -1963,6 +1970,14 @@ int adjoint_impl(Workspace *ws, const AdjointParams &P, const Boxes &b)
     // checkpoint_every == 0: every position of the forward run is kept (one
     // segment spanning the run, filled by the forward pass itself)
     const bool keep_all = checkpoint_every == 0;
+    // forward steps of small boxes in one launch each
+    const bool whole = keep_all && !g_opt.timer && !overlap(xN, 3 * N, m, N) &&
+                       !overlap(vN, 3 * N, m, N);
+    CHECK_RC(prepare_worklist(ws, 0, b, N, precision, x0, m, 1, s, false, !whole));
+    CHECK_RC(prepare_worklist(ws, 1, b, N, precision, x0, m, n_cot, s, lam_xN == nullptr));
+    const WorkList &wf = *ws->fwd;
+    const WorkList &wa = *ws->adj;
+    CHECK_RC(prepare_box_mass(ws, wf, m, s));
     const int64_t K = keep_all ? n_steps : checkpoint_every;
     const int64_t n_seg = (n_steps + K - 1) / K;
     CHECK_RC(ensure(ws->coef, (size_t)n_steps * sizeof(StepCoef)));
@@ -2021,8 +2036,7 @@ int adjoint_impl(Workspace *ws, const AdjointParams &P, const Boxes &b)
 
     // ---- forward with checkpoints --------------------------------------
     CHECK_HIP(hipMemcpyAsync(xw, x0, n3 * sizeof(double), hipMemcpyDeviceToDevice, s));
-    if (keep_all && wf.cfg.form == 4 && !g_opt.timer && !overlap(xN, 3 * N, m, N) &&
-        !overlap(vN, 3 * N, m, N)) {
+    if (whole && wf.cfg.form == 4) {
         // small boxes: a step per launch, from slot n to slot n + 1
         SmallArgs S = small_run_args(ws, wf, precision, m, N, G, ext, n_steps);
         S.v = const_cast<double *>(v0);  // read by row 0 alone
@@ -2388,7 +2402,7 @@ int run_he_impl(const RunParams &P, const Boxes &b)
     std::lock_guard<std::mutex> lock(g_mu);
     CHECK_RC(get_workspace(P.stream, ws));
     hipStream_t s = P.stream;
-    CHECK_RC(prepare_worklist(ws, 0, b, P.N, P.precision, P.x, P.m, 1, s));
+    CHECK_RC(prepare_worklist(ws, 0, b, P.N, P.precision, P.x, P.m, 1, s, false, true));
     const WorkList &wl = *ws->fwd;
     CHECK_RC(prepare_box_mass(ws, wl, P.m, s));
     const int64_t nsteps = P.last - P.first;
