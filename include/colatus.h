@@ -467,7 +467,8 @@ const char *colatus_strerror(int code);
                                      and the first capture costs a few ms)           */
 #define COLATUS_OPT_TIMER      2  /* 1: bracket every pair-sweep and integrator launch
                                      with hipEvents on its stream (default 0; the run
-                                     then launches eagerly instead of from a graph)  */
+                                     then launches eagerly instead of from a graph,
+                                     otherwise the same launches)                    */
 #define COLATUS_OPT_AUTOTUNE   3  /* 1: time candidate tile shapes on first use of an
                                      (N bucket, precision) and keep the fastest
                                      (default 0: built-in heuristic)                 */
@@ -521,7 +522,9 @@ int colatus_get_option(int key, int64_t *value);
 /* Kernel timer: sum of hipEvent durations (on the launching stream) of the
  * forward pair-sweep (kind 0), adjoint pair-sweep (kind 1) or run
  * integrator (kind 2) launches recorded since the last reset, and their
- * count.  Synchronises the recorded events.  reset != 0 clears.           */
+ * count.  A launch that makes the forces or a whole step of small boxes
+ * counts as a forward sweep.  Synchronises the recorded events.  reset != 0
+ * clears.                                                                  */
 int colatus_timer_read(int kind, double *total_ms, int64_t *launches, int reset);
 
 /* Tile shape the library would use (or has tuned) for N particles in one

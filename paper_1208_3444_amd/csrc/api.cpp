@@ -1088,9 +1088,9 @@ SmallArgs small_args(const WorkList &wl, int precision, const double *x, const d
     return A;
 }
 
-// Small boxes: the forces in the sweep's own launch, bracketed by the timer if
-// enabled.  Its blocks read x and m until the last of them has written.
-int run_small_forces(const WorkList &wl, bool mask, const SmallArgs &A, hipStream_t s)
+// Small boxes: the forces, or a whole step, in the sweep's own launch, bracketed by the
+// timer if enabled.  Its blocks read x and m until the last of them has written.
+int run_small(const WorkList &wl, bool mask, const SmallArgs &A, hipStream_t s)
 {
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (g_opt.timer) {
@@ -1506,7 +1506,7 @@ int enqueue_small_run(Workspace *ws, const RunParams &P, const WorkList &wl, boo
         A.x = buf[k & 1];
         A.x_out = k < n_steps ? buf[(k + 1) & 1] : (k & 1) ? P.x : nullptr;
         A.row = k;
-        CHECK_HIP(launch_small_box(wl.cfg, false, mask, wl.max_box, (int)wl.items.size(), A, s));
+        CHECK_RC(run_small(wl, mask, A, s));
     }
     return COLATUS_OK;
 }
@@ -1527,7 +1527,7 @@ int run_impl(const RunParams &P, const Boxes &b)
     const bool apart = !overlap(P.v, 3 * P.N, P.x, 3 * P.N) && !overlap(P.v, 3 * P.N, P.m, P.N) &&
                        !overlap(P.x, 3 * P.N, P.m, P.N);
     // steps of small boxes in one launch each
-    const bool whole = apart && !diag && !g_opt.graph && !g_opt.timer;
+    const bool whole = apart && !diag && !g_opt.graph;
     CHECK_RC(prepare_worklist(ws, 0, b, P.N, P.precision, P.x, P.m, 1, s, false, !whole));
     const WorkList &wl = *ws->fwd;
     CHECK_RC(prepare_box_mass(ws, wl, P.m, s));
@@ -1971,8 +1971,7 @@ int adjoint_impl(Workspace *ws, const AdjointParams &P, const Boxes &b)
     // segment spanning the run, filled by the forward pass itself)
     const bool keep_all = checkpoint_every == 0;
     // forward steps of small boxes in one launch each
-    const bool whole = keep_all && !g_opt.timer && !overlap(xN, 3 * N, m, N) &&
-                       !overlap(vN, 3 * N, m, N);
+    const bool whole = keep_all && !overlap(xN, 3 * N, m, N) && !overlap(vN, 3 * N, m, N);
     CHECK_RC(prepare_worklist(ws, 0, b, N, precision, x0, m, 1, s, false, !whole));
     CHECK_RC(prepare_worklist(ws, 1, b, N, precision, x0, m, n_cot, s, lam_xN == nullptr));
     const WorkList &wf = *ws->fwd;
@@ -2045,16 +2044,14 @@ int adjoint_impl(Workspace *ws, const AdjointParams &P, const Boxes &b)
             S.x = seg + (size_t)n * n3;
             S.x_out = seg + (size_t)(n + 1) * n3;
             S.row = n;
-            CHECK_HIP(launch_small_box(wf.cfg, false, mask, wf.max_box, (int)wf.items.size(), S,
-                                       s));
+            CHECK_RC(run_small(wf, mask, S, s));
         }
         if (xN || vN) {
             S.x = seg + (size_t)n_steps * n3;
             S.x_out = xN;
             S.v = vN;
             S.row = n_steps;
-            CHECK_HIP(launch_small_box(wf.cfg, false, mask, wf.max_box, (int)wf.items.size(), S,
-                                       s));
+            CHECK_RC(run_small(wf, mask, S, s));
         }
     } else {
         CHECK_HIP(launch_convert(0, v0, p, N, coef, 0, s));
@@ -2376,7 +2373,7 @@ int colatus_forces(const double *x, const double *m, int64_t N, double eps, doub
         A.ext = ext;
         A.acc = acc;
         A.phi = phi;
-        return run_small_forces(wl, mask, A, s);
+        return run_small(wl, mask, A, s);
     }
     CHECK_RC(prepare_box_mass(ws, wl, m, s));
     CHECK_RC(ensure(ws->part, (size_t)wl.max_slices * 3 * N * sizeof(double)));
@@ -2596,7 +2593,7 @@ int colatus_step(double *x, double *v, const double *m, int64_t N, double eps, d
         A.kick_p = p;
         A.kick_v = v;
         A.kick_coef = coef;
-        return run_small_forces(wl, mask, A, s);
+        return run_small(wl, mask, A, s);
     }
     CHECK_RC(run_forward_sweep(ws, wl, precision, false, mask, x, m, N, s, true));
     // g at the new positions into the cache (the comoving sum: a = 1), and
