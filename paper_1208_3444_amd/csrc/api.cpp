@@ -399,10 +399,11 @@ struct TuneKey {
     int nboxes_bucket;
     int precision;
     int kind;
+    bool many_cot = false;  // kind 1: more than kSymMaxCot cotangents
     bool operator<(const TuneKey &o) const
     {
-        return std::tie(nbucket, nboxes_bucket, precision, kind) <
-               std::tie(o.nbucket, o.nboxes_bucket, o.precision, o.kind);
+        return std::tie(nbucket, nboxes_bucket, precision, kind, many_cot) <
+               std::tie(o.nbucket, o.nboxes_bucket, o.precision, o.kind, o.many_cot);
     }
 };
 std::map<TuneKey, TileCfg> g_tuned;
@@ -1189,19 +1190,20 @@ int prepare_worklist(Workspace *ws, int kind, const Boxes &b, int64_t N, int pre
 {
     const int n_cu = cu_count(ws->device);
     TuneKey key{pow2_ceil(b.max_n), (int)std::min<size_t>(pow2_ceil(b.eps.size()), 1 << 20),
-                precision, kind};
-    TileCfg cfg;
-    auto it = g_tuned.find(key);
-    if (it != g_tuned.end()) {
-        cfg = it->second;
-    } else {
-        cfg = heuristic_cfg(b, precision, kind, n_cu, n_cot);
-        if (unit_cot && kind == 1 && precision == COLATUS_FP64 && g_opt.pair_form < 0 &&
-            matrix_adjoint(b, n_cot))
-            cfg = matrix_cfg(b, n_cu);
-        if (cfg.form == 4 && sums && precision != COLATUS_FP64 && b.max_n <= kSmallSums32)
-            cfg = small_boxes_cfg(b, 0);
-        if (g_opt.autotune && x && m) {
+                precision, kind, kind == 1 && n_cot > kSymMaxCot};
+    TileCfg cfg = heuristic_cfg(b, precision, kind, n_cu, n_cot);
+    if (unit_cot && kind == 1 && precision == COLATUS_FP64 && g_opt.pair_form < 0 &&
+        matrix_adjoint(b, n_cot))
+        cfg = matrix_cfg(b, n_cu);
+    if (cfg.form == 4 && sums && precision != COLATUS_FP64 && b.max_n <= kSmallSums32)
+        cfg = small_boxes_cfg(b, 0);
+    // the small and the matrix form have one shape each, chosen for the whole call:
+    // tuning compares sweeps of the other forms
+    if (cfg.form < 3) {
+        auto it = g_tuned.find(key);
+        if (it != g_tuned.end()) {
+            cfg = it->second;
+        } else if (g_opt.autotune && x && m) {
             // time candidates on the live data; scratch outputs only
             std::vector<TileCfg> cand;
             if (kind == 0) {
@@ -2289,8 +2291,10 @@ int colatus_tile_config(int64_t N, int precision, int kind, int32_t out[4])
     b.max_n = N;
     std::lock_guard<std::mutex> lock(g_mu);
     TuneKey key{pow2_ceil(N), 1, precision, kind};
+    TileCfg c = heuristic_cfg(b, precision, kind, n_cu);
     auto it = g_tuned.find(key);
-    TileCfg c = it != g_tuned.end() ? it->second : heuristic_cfg(b, precision, kind, n_cu);
+    if (c.form < 3 && it != g_tuned.end())
+        c = it->second;
     c = apply_overrides(c, kind, precision, b, n_cu);
     if (c.form == 4)  // adds the tiles and slices of this shape
         c = small_boxes_cfg(b, kind);
