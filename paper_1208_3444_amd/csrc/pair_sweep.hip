@@ -1816,16 +1816,17 @@ hipError_t dispatch_fwd_form(int form, const TileCfg &cfg, bool phi, bool mask, 
 }
 
 // Whether the ordered adjoint sweep takes the phased loop (adjoint_tile; FP32 pairs):
-// up to one block of four waves per CU it hides latency, and eight cotangents always
-// gain.  Plain / phased, us, equal masses, N = 4096 (256 blocks), 6145 (625) and
+// up to one block of four waves per CU it hides latency, and eight cotangents gain at
+// every size unless coincident pairs are masked.  Plain / phased, us, equal masses, N = 4096 (256 blocks), 6145 (625) and
 // 20 011: one cotangent 32.6 / 30.9, 39.2 / 42.0, 243 / 247; four 54.2 / 51.9, 80.0 /
 // 80.8, 512 / 519; eight 78.8 / 78.8, 153 / 151, 1031 / 1019.  Unequal masses gain
 // more (one cotangent 39.6 / 32.4, 44.7 / 43.9, 270 / 266), but a kernel with each
-// loop for its masses runs the plain one slower (N = 4097: 31.6 -> 34.0).  FP64
-// instructions are never paired, and batching them measured 1 % slower.
-template <typename T, int C> bool adj_phased(int n_items)
+// loop for its masses runs the plain one slower (N = 4097: 31.6 -> 34.0).  Eight
+// cotangents with the mask, a whole call: 11 000 particles 481 / 494, 32 768 3117 /
+// 3167.  FP64 instructions are never paired, and batching them measured 1 % slower.
+template <typename T, int C> bool adj_phased(bool mask, int n_items)
 {
-    return sizeof(T) == 4 && (C == 8 || n_items <= 256);
+    return sizeof(T) == 4 && ((C == 8 && !mask) || n_items <= 256);
 }
 
 template <typename T, int ACC, int R, int TPB, int C, bool MASK, bool PHASED>
@@ -1850,7 +1851,7 @@ hipError_t launch_adj(bool mask, const double *x, const double *m, int64_t N, co
                       stream);
     };
     if constexpr (sizeof(T) == 4)
-        if (adj_phased<T, C>(n_items))
+        if (adj_phased<T, C>(mask, n_items))
             return mask ? go(launch_adj_k<T, ACC, R, TPB, C, true, true>)
                         : go(launch_adj_k<T, ACC, R, TPB, C, false, true>);
     return mask ? go(launch_adj_k<T, ACC, R, TPB, C, true, false>)
