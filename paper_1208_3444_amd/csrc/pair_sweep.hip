@@ -580,7 +580,8 @@ __device__ __forceinline__ void sym_chunk(T sx, T sy, T sz, T sm, T &qx, T &qy, 
 // are folded every 256 sources; with at most 256 every partial sum (a
 // target's from one part, a source's reaction from one part) is a single
 // FP32 sum of at most 256 terms, like the ordered loop's per-tile partials.
-template <typename T, int ACC, int R, int W, bool FOLD, bool REACT, bool PHI, bool MASK>
+template <typename T, int ACC, int R, int W, bool FOLD, bool REACT, bool PHI, bool MASK,
+          bool PHASED>
 __device__ __forceinline__ void sym_item(const WorkItem &w, const double *__restrict__ X,
                                          const double *__restrict__ Y,
                                          const double *__restrict__ Z,
@@ -658,11 +659,11 @@ __device__ __forceinline__ void sym_item(const WorkItem &w, const double *__rest
         }
         T qx = (T)0.0, qy = (T)0.0, qz = (T)0.0, qp = (T)0.0;
         if (eqm)
-            sym_chunk<T, R, REACT, true, PHI, MASK, true>(sx, sy, sz, sm, qx, qy, qz, qp, xi, yi, zi,
-                                                       mi, eps2, ax, ay, az, ap);
+            sym_chunk<T, R, REACT, true, PHI, MASK, PHASED>(sx, sy, sz, sm, qx, qy, qz, qp, xi, yi, zi,
+                                                         mi, eps2, ax, ay, az, ap);
         else
-            sym_chunk<T, R, REACT, false, PHI, MASK, true>(sx, sy, sz, sm, qx, qy, qz, qp, xi, yi, zi,
-                                                        mi, eps2, ax, ay, az, ap);
+            sym_chunk<T, R, REACT, false, PHI, MASK, PHASED>(sx, sy, sz, sm, qx, qy, qz, qp, xi, yi, zi,
+                                                          mi, eps2, ax, ay, az, ap);
         if constexpr (FOLD) {
             if ((c & 3) == 3 || c == n_chunks - 1) {
 #pragma unroll
@@ -785,11 +786,11 @@ __device__ __forceinline__ void sym_item(const WorkItem &w, const double *__rest
     }
 }
 
-// One wave per workgroup with four targets per lane is held to 96 VGPRs so
-// that five waves share each SIMD.
-template <typename T, int ACC, int R, int W, bool PHI, bool MASK>
+// One wave per workgroup with four targets per lane is held to 96 VGPRs (80 with the
+// plain loop) so that five (six) waves share each SIMD.
+template <typename T, int ACC, int R, int W, bool PHI, bool MASK, bool PHASED>
 __global__ __launch_bounds__(64 * W)
-__attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && R * W == 4 ? 5 : 1))) void
+__attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 || R * W != 4 ? 1 : PHASED ? 5 : 6))) void
 pair_sweep_sym_kernel(
     const double *__restrict__ x, const double *__restrict__ m, int64_t N,
     const WorkItem *__restrict__ items, int n_items, int *__restrict__ counter,
@@ -810,11 +811,11 @@ pair_sweep_sym_kernel(
             break;
         const WorkItem w = items[it];
         if (w.kind == 0)
-            sym_item<T, ACC, R, W, FOLD, true, PHI, MASK>(w, X, Y, Z, m, N, box_mass, part,
-                                                       part_phi, red, react);
+            sym_item<T, ACC, R, W, FOLD, true, PHI, MASK, PHASED>(w, X, Y, Z, m, N, box_mass, part,
+                                                                  part_phi, red, react);
         else
-            sym_item<T, ACC, 1, W, FOLD, false, PHI, MASK>(w, X, Y, Z, m, N, box_mass, part,
-                                                        part_phi, red, react);
+            sym_item<T, ACC, 1, W, FOLD, false, PHI, MASK, PHASED>(w, X, Y, Z, m, N, box_mass,
+                                                                   part, part_phi, red, react);
     }
 }
 
@@ -1664,10 +1665,10 @@ struct FwdArgs {
     hipStream_t s;
 };
 
-template <typename T, int ACC, int R, int W, bool PHI, bool MASK>
+template <typename T, int ACC, int R, int W, bool PHI, bool MASK, bool PHASED>
 hipError_t launch_sym(const FwdArgs &a)
 {
-    auto k = pair_sweep_sym_kernel<T, ACC, R, W, PHI, MASK>;
+    auto k = pair_sweep_sym_kernel<T, ACC, R, W, PHI, MASK, PHASED>;
     int grid = a.persistent ? persistent_grid(k, 64 * W, 0, a.n_items) : a.n_items;
     if (grid <= 0)
         return hipSuccess;
@@ -1677,14 +1678,27 @@ hipError_t launch_sym(const FwdArgs &a)
     return hipGetLastError();
 }
 
-template <typename T, int ACC, int R, int W>
+template <typename T, int ACC, int R, int W, bool PHASED>
 hipError_t dispatch_sym_flags(bool phi, bool mask, const FwdArgs &a)
 {
     if (phi)
-        return mask ? launch_sym<T, ACC, R, W, true, true>(a)
-                    : launch_sym<T, ACC, R, W, true, false>(a);
-    return mask ? launch_sym<T, ACC, R, W, false, true>(a)
-                : launch_sym<T, ACC, R, W, false, false>(a);
+        return mask ? launch_sym<T, ACC, R, W, true, true, PHASED>(a)
+                    : launch_sym<T, ACC, R, W, true, false, PHASED>(a);
+    return mask ? launch_sym<T, ACC, R, W, false, true, PHASED>(a)
+                : launch_sym<T, ACC, R, W, false, false, PHASED>(a);
+}
+
+// The loop of a sweep of single items, by its waves of part pairs (of all items, FP64)
+// as the grouped one's (sym_phased).  Plain / phased, us, FP32 pairs: R = 4, one wave,
+// 11 000 particles (903 pairs) 49.7 / 51.3; R = 8 and R = 4 with two waves, 8000 (120
+// pairs) 134 / 141 and 77.6 / 83.2.  FP64 8000 (496 pairs) 59.8 / 62.6.
+template <typename T, int ACC, int R, int W>
+hipError_t dispatch_sym_items(const TileCfg &cfg, bool phi, bool mask, const FwdArgs &a)
+{
+    const int64_t waves = (sizeof(T) == 8 ? (int64_t)a.n_items : cfg.pairs) * W;
+    return waves > (sizeof(T) == 8 || R * W == 4 ? 1024 : 640)
+               ? dispatch_sym_flags<T, ACC, R, W, true>(phi, mask, a)
+               : dispatch_sym_flags<T, ACC, R, W, false>(phi, mask, a);
 }
 
 // Whether a grouped sweep takes the phased loop (sym_chunk), which pays once most
@@ -1755,16 +1769,16 @@ hipError_t dispatch_sym(const TileCfg &cfg, bool phi, bool mask, const FwdArgs &
     }
     if constexpr (sizeof(T) == 4) {
         if (cfg.R == 4 && cfg.tpb == 64)
-            return dispatch_sym_flags<T, ACC, 4, 1>(phi, mask, a);
+            return dispatch_sym_items<T, ACC, 4, 1>(cfg, phi, mask, a);
         if (cfg.R == 8 && cfg.tpb == 64)
-            return dispatch_sym_flags<T, ACC, 8, 1>(phi, mask, a);
+            return dispatch_sym_items<T, ACC, 8, 1>(cfg, phi, mask, a);
         if (cfg.R == 4 && cfg.tpb == 128)
-            return dispatch_sym_flags<T, ACC, 4, 2>(phi, mask, a);
+            return dispatch_sym_items<T, ACC, 4, 2>(cfg, phi, mask, a);
     } else {
         if (cfg.R == 4 && cfg.tpb == 64)
-            return dispatch_sym_flags<T, ACC, 4, 1>(phi, mask, a);
+            return dispatch_sym_items<T, ACC, 4, 1>(cfg, phi, mask, a);
         if (cfg.R == 2 && cfg.tpb == 128)
-            return dispatch_sym_flags<T, ACC, 2, 2>(phi, mask, a);
+            return dispatch_sym_items<T, ACC, 2, 2>(cfg, phi, mask, a);
     }
     return hipErrorInvalidValue;
 }

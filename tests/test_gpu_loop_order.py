@@ -69,3 +69,28 @@ def test_adjoint_of_a_box_alone_and_among_others(dev, C, eps, equal, prec):
         colatus.set_option(colatus.OPT_TILE_SLICES, 0)
     assert float(one.abs().max()) > 1e-10
     assert torch.equal(one, many[..., :n]) and torch.equal(one, many[..., -n:])
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed_twosum", "mixed_f64acc", "fp32"])
+@pytest.mark.parametrize("R,tpb,n,copies", [(4, 64, 300, 1200), (8, 64, 700, 700),
+                                            (4, 128, 700, 700), (2, 128, 300, 1200)])
+def test_single_items_alone_and_among_others(dev, R, tpb, n, copies, prec):
+    """The symmetric sweep of one item per workgroup, at its own tile shapes."""
+    if (prec == "fp64") != ((R, tpb) == (2, 128)) and (R, tpb) != (4, 64):
+        pytest.skip("no such shape")
+    x, m = inputs.random_cloud(n, n, scale=0.5)
+    off = np.arange(copies + 1) * n
+    for key, value in ((colatus.OPT_PAIR_FORM, 2), (colatus.OPT_PAIR_GROUP, 0),
+                       (colatus.OPT_TILE_R, R), (colatus.OPT_TILE_TPB, tpb)):
+        colatus.set_option(key, value)
+    try:
+        one, p1 = colatus.forces(to_dev(x, dev), to_dev(m, dev), 0.02, precision=prec,
+                                 with_phi=True)
+        many, phi = colatus.forces(to_dev(np.tile(x, copies), dev), to_dev(np.tile(m, copies), dev),
+                                   0.0, precision=prec, with_phi=True,
+                                   batch=(off, np.full(copies, 0.02)))
+    finally:
+        for key, value in ((colatus.OPT_PAIR_FORM, -1), (colatus.OPT_PAIR_GROUP, 1),
+                           (colatus.OPT_TILE_R, 0), (colatus.OPT_TILE_TPB, 0)):
+            colatus.set_option(key, value)
+    assert torch.equal(many[:, :n], one) and torch.equal(phi[-n:], p1)
