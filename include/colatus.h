@@ -471,7 +471,9 @@ const char *colatus_strerror(int code);
                                      otherwise the same launches)                    */
 #define COLATUS_OPT_AUTOTUNE   3  /* 1: time candidate tile shapes on first use of an
                                      (N bucket, precision) and keep the fastest
-                                     (default 0: built-in heuristic)                 */
+                                     (default 0: built-in heuristic; the one-launch
+                                     form of small boxes and the matrix products of
+                                     colatus_ftle stay as they are)                  */
 #define COLATUS_OPT_TILE_R     4  /* >0: force targets per lane of the forward sweep
                                      (forms 0, 1: 1, 2, 4; form 2: 4 or 8 with 64
                                      threads, or 4 with 128 for FP32 pairs; 4 with
@@ -498,10 +500,16 @@ const char *colatus_strerror(int code);
                                      adjoint pair terms change sign when the two
                                      particles swap), boxes cut into parts of
                                      R x threads particles; -1 (default) = the
-                                     heuristic's or the autotuner's choice (2 for
+                                     heuristic's or the autotuner's choice: 2 for
                                      the forward up to 2^18 particles per box and
-                                     for the adjoint with up to 3 cotangents, else
-                                     0).  FP64 pairs: 1 means 0                      */
+                                     for the adjoint with up to 3 cotangents, 0 for
+                                     more of either and for boxes too small to fill
+                                     the GPU with symmetric items; the smallest (up
+                                     to 4096 particles with FP32 pairs, 6144 with
+                                     FP64) take a form of their own, the ordered
+                                     pairs finished in one launch, and
+                                     colatus_ftle's sums of FP64 pairs matrix
+                                     products.  FP64 pairs: 1 means 0                */
 #define COLATUS_OPT_ROCTX      9  /* 1: a roctx range around every call, named after
                                      the entry point, and one per step of the
                                      eagerly launched loops (graph-replayed steps
@@ -531,7 +539,10 @@ int colatus_timer_read(int kind, double *total_ms, int64_t *launches, int reset)
  * box at the given precision: out[0] = targets per lane R, out[1] = threads
  * per block, out[2] = source slices (form 2: the parts P of R x threads
  * particles), out[3] = pair-loop form (see COLATUS_OPT_PAIR_FORM).  kind 0 =
- * forward, 1 = adjoint.  A forward form 2 with R = 4 and 64 threads runs in
+ * forward, 1 = adjoint.  Boxes small enough for the one-launch form answer
+ * with the ordered shape (form 0) that an option set to it would run: the same
+ * sums with FP32 pairs, in another order with FP64 ones.  colatus_ftle's
+ * matrix products have no shape to ask for.  A forward form 2 with R = 4 and 64 threads runs in
  * 2x2 groups of part pairs while COLATUS_OPT_PAIR_GROUP is 1, and then
  * writes ceil(P/2) + 1 partial-sum slots per particle (P = 1: one) instead
  * of P.                                                                    */

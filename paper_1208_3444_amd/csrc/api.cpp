@@ -2296,7 +2296,7 @@ int colatus_tile_config(int64_t N, int precision, int kind, int32_t out[4])
     if (c.form < 3 && it != g_tuned.end())
         c = it->second;
     c = apply_overrides(c, kind, precision, b, n_cu);
-    if (c.form == 4)  // adds the tiles and slices of this shape
+    if (c.form == 4)  // the ordered shape it stands for (FP32 pairs: the same sums)
         c = small_boxes_cfg(b, kind);
     out[0] = c.R;
     out[1] = c.tpb;

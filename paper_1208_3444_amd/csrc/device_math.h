@@ -42,6 +42,18 @@ __device__ __forceinline__ double fma_t(double a, double b, double c) { return f
 // wave priority (s_setprio), which lets one wave finish its burst while the
 // others wait at theirs and then run their FMAs side by side.  burst_begin /
 // burst_end bracket such a run; neither lets the compiler move code across.
+__device__ __forceinline__ void phase_mark() { __builtin_amdgcn_sched_barrier(0); }
+__device__ __forceinline__ void burst_begin()
+{
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(1);
+}
+__device__ __forceinline__ void burst_end()
+{
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(0);
+}
+
 // A constant held in a vector register: an FP32 instruction with a scalar or
 // literal operand is never paired (4.1 cycles instead of 2.1).
 __device__ __forceinline__ float in_vgpr(float c)
@@ -61,16 +73,14 @@ __device__ __forceinline__ float select_value(bool c, float v, float other)
     asm volatile("" : "+v"(v));
     return c ? v : other;
 }
-__device__ __forceinline__ void phase_mark() { __builtin_amdgcn_sched_barrier(0); }
-__device__ __forceinline__ void burst_begin()
+
+// Orders the LDS accesses of a wave's lanes (no instruction is needed: a wave's LDS
+// operations complete in order).
+__device__ __forceinline__ void wave_lds_fence()
 {
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_setprio(1);
-}
-__device__ __forceinline__ void burst_end()
-{
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // The potential sweep includes the self pair j == k, whose term is exactly

@@ -65,15 +65,6 @@ __device__ void time_integrals(const Cosmo &c, double s0, double s1, double out[
         out[q] = 0.5 * h * acc[q];
 }
 
-// Orders the lanes' LDS accesses within a wave (no instruction is needed: a
-// wave's LDS operations complete in order).
-__device__ __forceinline__ void wave_lds_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Working space of the sixteen lanes that share one step.
 struct CoefShared {
     double wh[2][8], ia[2][8];  // weight / H and 1 / a at the nodes of each half step

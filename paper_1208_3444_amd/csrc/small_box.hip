@@ -118,14 +118,6 @@ __device__ __forceinline__ double small_mass(const SmallArgs &A, const WorkItem 
     return __syncthreads_or(differ) ? NAN : m0;
 }
 
-// Orders the LDS accesses of a wave's lanes (they complete in order).
-__device__ __forceinline__ void wave_lds_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // A tile's sources in order, eight at a time (the next eight on their way from
 // LDS: few waves are there to hide the latencies), in the phases of sweep_tile.
 template <bool PHI, bool MASK, bool EQM>
@@ -359,7 +351,7 @@ __device__ __forceinline__ void small_loop64(const double *__restrict__ X,
             const double dx = px - tx[t], dy = py - ty[t], dz = pz - tz[t];
             const double s = fma(dz, dz, fma(dy, dy, fma(dx, dx, eps2)));
             // s^{-3/2} from the estimate y, y^3 (1 - e)^{-3/2} to second order in
-            // e = 1 - s y^2 (below 1e-7): as many operations as refining y first,
+            // e = 1 - s y^2 (below 1.2e-7): as many operations as refining y first,
             // and 3e-15 closer
             const double y = rsq_raw(s), y2 = y * y, e = fma(-s, y2, 1.0), y3 = y2 * y;
             const double r3 = fma(y3, e * fma(1.875, e, 1.5), y3);

@@ -33,6 +33,10 @@
 // 74 us; 64 tracers, 301 rows 20.5 / 14.1 us, 4096 rows 1394 / 125 us; below
 // about 160 rows both are bound by their two launches (12-13 us).  4096 rows
 // fill a CU's LDS.
+// Accuracy, direct / FFT, against extended precision, 1001 rows: noise 1.3e-15 /
+// 7e-16 of the mean power (rms), a decaying velocity 2e-14 / 5e-15; in bins far
+// below the strongest the FFT's rounding floor is the higher one, about twice in
+// amplitude (1e-15 of the series' norm).
 #include "colatus_internal.h"
 
 #include <hip/hip_runtime.h>
