@@ -30,6 +30,21 @@ __device__ __forceinline__ double rinv3_from(double s, double y)
     return fma(1.5 * e, y3, y3);
 }
 
+// The same with one term more, two of (1 - e)^{-1/2} and of (1 - e)^{-3/2} (|e| < 1.2e-7),
+// within rounding of exact: the periodic sum's pairs.
+__device__ __forceinline__ double rsqrt_exact(double s, double y)
+{
+    const double e = fma(-s, y * y, 1.0);
+    return fma(y * e, fma(0.375, e, 0.5), y);
+}
+__device__ __forceinline__ double rinv3_exact(double s, double y)
+{
+    const double y2 = y * y;
+    const double e = fma(-s, y2, 1.0);
+    const double y3 = y2 * y;
+    return fma(y3 * e, fma(1.875, e, 1.5), y3);
+}
+
 __device__ __forceinline__ float fma_t(float a, float b, float c) { return fmaf(a, b, c); }
 __device__ __forceinline__ double fma_t(double a, double b, double c) { return fma(a, b, c); }
 

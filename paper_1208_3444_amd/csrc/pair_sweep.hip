@@ -1972,21 +1972,6 @@ struct EwaldReal {
                          // Phi r^{-1} (kWindowDegree + 2)
 };
 
-// s^{-1/2} and s^{-3/2} from y = v_rsq_f64(s), e = 1 - s y^2 (|e| < 1.2e-7): two
-// terms of (1 - e)^{-1/2} and (1 - e)^{-3/2}, within rounding of exact.
-__device__ __forceinline__ double rsqrt_exact(double s, double y)
-{
-    const double e = fma(-s, y * y, 1.0);
-    return fma(y * e, fma(0.375, e, 0.5), y);
-}
-__device__ __forceinline__ double rinv3_exact(double s, double y)
-{
-    const double y2 = y * y;
-    const double e = fma(-s, y2, 1.0);
-    const double y3 = y2 * y;
-    return fma(y3 * e, fma(1.875, e, 1.5), y3);
-}
-
 __device__ __forceinline__ double wrap_image(double d, double L)
 {
     return d - L * rint(d / L);
@@ -2001,7 +1986,7 @@ __device__ __forceinline__ double wrap_image(double d, double L)
 // same word: kept in registers they take half the waves, and scalar loads in
 // the loop wait too long (20^3 / 32^3 evaluations: 275 / 1304 us so, 258 / 1317
 // kept in registers, 460 / 1577 by scalar loads).  Bound by FP64 issue; with
-// the math library's erf and exp (about 180 issue slots per pair; about 85 now)
+// the math library's erf and exp (about 180 issue slots per pair; 76 now, counted)
 // a 32^3 evaluation took 2.95 ms.
 template <int R, bool REACT, bool PHI>
 __device__ __forceinline__ void ewald_chunk(bool wx, bool wy, bool wz, double sx, double sy, double sz, double sm, double &qx,

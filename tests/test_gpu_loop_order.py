@@ -71,13 +71,15 @@ def test_adjoint_of_a_box_alone_and_among_others(dev, C, eps, equal, prec):
     assert torch.equal(one, many[..., :n]) and torch.equal(one, many[..., -n:])
 
 
-@pytest.mark.parametrize("prec", ["fp64", "mixed_twosum", "mixed_f64acc", "fp32"])
-@pytest.mark.parametrize("R,tpb,n,copies", [(4, 64, 300, 1200), (8, 64, 700, 700),
-                                            (4, 128, 700, 700), (2, 128, 300, 1200)])
+FP32_PAIRS = ("mixed_twosum", "mixed_f64acc", "fp32")
+
+
+@pytest.mark.parametrize("R,tpb,n,copies,prec",
+                         [(4, 64, 300, 1200, p) for p in FP32_PAIRS + ("fp64",)] +
+                         [(8, 64, 700, 700, p) for p in FP32_PAIRS] +
+                         [(4, 128, 700, 700, p) for p in FP32_PAIRS] + [(2, 128, 300, 1200, "fp64")])
 def test_single_items_alone_and_among_others(dev, R, tpb, n, copies, prec):
     """The symmetric sweep of one item per workgroup, at its own tile shapes."""
-    if (prec == "fp64") != ((R, tpb) == (2, 128)) and (R, tpb) != (4, 64):
-        pytest.skip("no such shape")
     x, m = inputs.random_cloud(n, n, scale=0.5)
     off = np.arange(copies + 1) * n
     for key, value in ((colatus.OPT_PAIR_FORM, 2), (colatus.OPT_PAIR_GROUP, 0),
