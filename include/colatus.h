@@ -291,7 +291,8 @@ int colatus_run_he(double *x, double *v, const double *m, int64_t N, double eps,
  *   phi_k = -G [sum_{j != k} m_j Psi(x_j - x_k) + m_k Psi_self], with Psi the
  * matching potential (real part erfc(alpha r)/r, the nearest image's
  * Plummer correction, reciprocal part exp(-q^2/4 alpha^2)/q^2 cos(q . d),
- * constant -pi / (alpha^2 L^3)) and Psi_self the particle's own images and
+ * constant -pi / (alpha^2 L^3); for two particles at the same place its limit,
+ * at eps == 0 without the infinite 1 / r) and Psi_self the particle's own images and
  * background (-2.8372974794806 / L for one particle: the simple cubic
  * Madelung constant).  The library takes the splitting and its cutoffs so
  * that the neglected real-space images and reciprocal terms fall below 1e-15

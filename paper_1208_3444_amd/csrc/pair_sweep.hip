@@ -1954,10 +1954,11 @@ hipError_t dispatch_adj(const TileCfg &cfg, bool mask, const double *x, const do
 // kernel ends, to the precision's resolution, at half the box).  FP32 pairs:
 // Phi = erf(alpha r), P = erf(u) - (2u / sqrt(pi)) e^{-u^2}, u = alpha r.  FP64
 // pairs: the prolate window (ewald_window.h), whose Phi / r and P / r^3 are
-// polynomials in r^2 up to r_c = L / 2 and 1 / r and 1 / r^3 beyond.  r == 0 (a
-// part's own particle, or coincident particles): w = 0 and psi = (eps^2)^{-1/2}
-// (0 at eps == 0), the value the open-box loop gives its self pair and the
-// O(N) kernels remove.
+// polynomials in r^2 up to r_c = L / 2 and 1 / r and 1 / r^3 beyond.  r == 0: w = 0; a
+// part's own particle has psi = (eps^2)^{-1/2} (0 at eps == 0), the value the
+// open-box loop gives its self pair and the O(N) kernels remove, and its smooth
+// part is the self term's; another particle at the same place has psi less the
+// limit of Phi / r.
 // FP64 pairs take coordinates relative to the item's first target, each
 // wrapped to its nearest image before the subtraction, and wrap the pair's
 // separation once more.  FP32 pairs take 32-bit fixed-point coordinates
@@ -1977,10 +1978,17 @@ __device__ __forceinline__ double wrap_image(double d, double L)
     return d - L * rint(d / L);
 }
 
+// Whether source chunk c of an item holds its targets (a piece of a diagonal part):
+// each lane then meets its own particle in the chunk's first step.
+__device__ __forceinline__ bool own_chunk(const WorkItem &w, int c)
+{
+    return w.j0 + (int64_t)c * 64 == w.i0;
+}
+
 // 64 steps of one source chunk (sources travel around the wave as in
-// sym_chunk) against the lane's R targets, FP64.  wx, wy, wz: this axis'
-// separations may exceed half the box (ewald_item) and are wrapped to the
-// nearest image.  A step whose pairs all lie beyond r_c skips the polynomials,
+// sym_chunk) against the lane's R targets, FP64.  own: see own_chunk.  wx, wy, wz:
+// this axis' separations may exceed half the box (ewald_item) and are wrapped to
+// the nearest image.  A step whose pairs all lie beyond r_c skips the polynomials,
 // one whose pairs all lie within it the second square root.  The polynomials'
 // constants are read from LDS at the start of every step, every lane the
 // same word: kept in registers they take half the waves, and scalar loads in
@@ -1989,13 +1997,14 @@ __device__ __forceinline__ double wrap_image(double d, double L)
 // the math library's erf and exp (about 180 issue slots per pair; 76 now, counted)
 // a 32^3 evaluation took 2.95 ms.
 template <int R, bool REACT, bool PHI>
-__device__ __forceinline__ void ewald_chunk(bool wx, bool wy, bool wz, double sx, double sy, double sz, double sm, double &qx,
+__device__ __forceinline__ void ewald_chunk(bool own, bool wx, bool wy, bool wz, double sx,
+                                            double sy, double sz, double sm, double &qx,
                                             double &qy, double &qz, double &qp,
                                             const double (&xi)[R], const double (&yi)[R],
                                             const double (&zi)[R], const double (&mi)[R],
-                                            double eps2, const EwaldReal &E,
-                                            const double *spoly, double (&ax)[R], double (&ay)[R],
-                                            double (&az)[R], double (&ap)[R])
+                                            double eps2, const EwaldReal &E, const double *spoly,
+                                            double (&ax)[R], double (&ay)[R], double (&az)[R],
+                                            double (&ap)[R])
 {
 #pragma unroll 1
     for (int k = 0; k < 64; ++k) {
@@ -2079,7 +2088,9 @@ __device__ __forceinline__ void ewald_chunk(bool wx, bool wy, bool wz, double sx
             ay[r] = fma(wt, dy[r], ay[r]);
             az[r] = fma(wt, dz[r], az[r]);
             if constexpr (PHI) {
-                psi[r] = nz ? psi[r] - S[r] : eps2 > 0.0 ? psi[r] : 0.0;
+                // a particle's own smooth part is left to the self term
+                const double soft = nz || eps2 > 0.0 ? psi[r] : 0.0;
+                psi[r] = !nz && own && k == 0 ? soft : soft - S[r];
                 ap[r] = fma(sm, psi[r], ap[r]);
             }
             if constexpr (REACT) {
@@ -2167,8 +2178,8 @@ __device__ __forceinline__ void ewald_item(const WorkItem &w, const double *__re
         const bool wx = !__all(fabs(sx - bx) <= ex), wy = !__all(fabs(sy - by) <= ey),
                    wz = !__all(fabs(sz - bz) <= ez);
         double qx = 0.0, qy = 0.0, qz = 0.0, qp = 0.0;
-        ewald_chunk<R, REACT, PHI>(wx, wy, wz, sx, sy, sz, sm, qx, qy, qz, qp, xi, yi, zi, mi,
-                                   eps2, E, spoly, ax, ay, az, ap);
+        ewald_chunk<R, REACT, PHI>(own_chunk(w, c), wx, wy, wz, sx, sy, sz, sm, qx, qy, qz, qp, xi,
+                                   yi, zi, mi, eps2, E, spoly, ax, ay, az, ap);
         if constexpr (REACT) {
             if (jv) {
                 const int64_t rs = (int64_t)w.rslice;
@@ -2207,7 +2218,8 @@ struct EwaldFx {
     float c_exp;     // -alpha^2 log2(e): exp(-alpha^2 r^2) = 2^(c_exp r^2)
     float c_t;       // 0.3275911 alpha
     float c_g;       // (2 / sqrt(pi)) alpha
-    float phi_self;  // the r = 0 potential term: (eps^2)^{-1/2}, 0 at eps = 0
+    float phi_self;  // the own particle's potential term: (eps^2)^{-1/2}, 0 at eps = 0
+    float phi_same;  // another particle's at r = 0: less the limit of erf(alpha r) / r
 };
 
 __device__ __forceinline__ uint32_t fx_coord(double x, double scale)
@@ -2235,7 +2247,7 @@ __device__ __forceinline__ uint32_t wave_rotate_back_u(uint32_t v)
 // P(u) = erf(u) - (2 / sqrt(pi)) u g = 1 - g (t p + c_g r).  (Folding c_g
 // into the exponent as 2^(c_exp r^2 + log2 c_g) would save the product c_g r
 // but raises the exponent's rounding error sixfold.)  At r = 0 the pair's
-// terms are selected (w = 0, psi = phi_self), not branched to, so that the
+// terms are selected (w = 0, psi = phi0), not branched to, so that the
 // target rows interleave.
 //
 // 64 steps of one source chunk, in the phases of sym_chunk: separations; a
@@ -2286,7 +2298,7 @@ __device__ __forceinline__ void ewald_fx_roots(const EwaldFxRegs &C, const float
 
 // w (and psi) of one pair from its roots, t = 1 / (1 + 0.3275911 u).
 template <bool PHI>
-__device__ __forceinline__ float ewald_fx_weight(const EwaldFxRegs &C, float phi_self, float r2,
+__device__ __forceinline__ float ewald_fx_weight(const EwaldFxRegs &C, float phi0, float r2,
                                                  float rs, float ri, float r, float g, float t,
                                                  float &psi)
 {
@@ -2295,18 +2307,19 @@ __device__ __forceinline__ float ewald_fx_weight(const EwaldFxRegs &C, float phi
     const bool nz = r2 > 0.0f;
     if constexpr (PHI) {
         const float erf_u = fmaf(-t * p, g, C.one);
-        psi = select_value(nz, fmaf(-erf_u, ri, rs), phi_self);
+        psi = select_value(nz, fmaf(-erf_u, ri, rs), phi0);
     }
     return select_value(nz, fmaf(-P, ri * (ri * ri), rs * (rs * rs)), 0.0f);
 }
 
 template <int R, bool REACT, bool PHI>
-__device__ __forceinline__ void ewald_chunk_fx(uint32_t sx, uint32_t sy, uint32_t sz, float sm,
-                                               float &qx, float &qy, float &qz, float &qp,
-                                               const uint32_t (&xi)[R], const uint32_t (&yi)[R],
-                                               const uint32_t (&zi)[R], const float (&mi)[R],
-                                               const EwaldFx &E, float (&ax)[R], float (&ay)[R],
-                                               float (&az)[R], float (&ap)[R])
+__device__ __forceinline__ void ewald_chunk_fx(bool own, uint32_t sx, uint32_t sy, uint32_t sz,
+                                               float sm, float &qx, float &qy, float &qz,
+                                               float &qp, const uint32_t (&xi)[R],
+                                               const uint32_t (&yi)[R], const uint32_t (&zi)[R],
+                                               const float (&mi)[R], const EwaldFx &E,
+                                               float (&ax)[R], float (&ay)[R], float (&az)[R],
+                                               float (&ap)[R])
 {
     constexpr int U = R == 1 && !REACT ? 4 : 1;
     constexpr int B = U * R;
@@ -2358,8 +2371,9 @@ __device__ __forceinline__ void ewald_chunk_fx(uint32_t sx, uint32_t sy, uint32_
             for (int q = 0; q < R; ++q) {
                 const int b = u * R + q;
                 float psi = 0.0f;
-                const float w = ewald_fx_weight<PHI>(C, E.phi_self, r2[b], rs[b], ri[b], r[b],
-                                                     g[b], t[b], psi);
+                const float phi0 = own && k + u == 0 ? E.phi_self : E.phi_same;
+                const float w = ewald_fx_weight<PHI>(C, phi0, r2[b], rs[b], ri[b], r[b], g[b], t[b],
+                                                     psi);
                 const float wt = su[u] * w;
                 ax[q] = fmaf(wt, dx[b], ax[q]);
                 ay[q] = fmaf(wt, dy[b], ay[q]);
@@ -2446,7 +2460,7 @@ __device__ __forceinline__ void ewald_react_fx(const WorkItem &w, const double *
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             float psi = 0.0f;
-            const float wq = ewald_fx_weight<PHI>(C, E.phi_self, r2[q], rs[q], ri[q], r[q], g[q],
+            const float wq = ewald_fx_weight<PHI>(C, E.phi_same, r2[q], rs[q], ri[q], r[q], g[q],
                                                   t[q], psi);
             const float ws = mi[q] * wq;
             qx = fmaf(ws, dx[q], qx);
@@ -2477,6 +2491,7 @@ __device__ __forceinline__ EwaldFx ewald_fx(double eps2, double sc, double alpha
     E.c_t = (float)(0.3275911 * a_fx);
     E.c_g = (float)(1.1283791670955126 * a_fx);
     E.phi_self = E.eps2 > 0.0f ? __builtin_amdgcn_rsqf(E.eps2) : 0.0f;
+    E.phi_same = E.phi_self - E.c_g;
     return E;
 }
 
@@ -2522,8 +2537,8 @@ __device__ __forceinline__ void ewald_item_fx(const WorkItem &w, const double *_
             sm = (float)m[j];
         }
         float qx = 0.0f, qy = 0.0f, qz = 0.0f, qp = 0.0f;
-        ewald_chunk_fx<R, REACT, PHI>(sx, sy, sz, sm, qx, qy, qz, qp, xi, yi, zi, mi, E, ax, ay,
-                                      az, ap);
+        ewald_chunk_fx<R, REACT, PHI>(own_chunk(w, c), sx, sy, sz, sm, qx, qy, qz, qp, xi, yi, zi,
+                                      mi, E, ax, ay, az, ap);
         if constexpr (REACT) {
             if (jv) {
                 const int64_t rs = (int64_t)w.rslice;
