@@ -1978,17 +1978,10 @@ __device__ __forceinline__ double wrap_image(double d, double L)
     return d - L * rint(d / L);
 }
 
-// Whether source chunk c of an item holds its targets (a piece of a diagonal part):
-// each lane then meets its own particle in the chunk's first step.
-__device__ __forceinline__ bool own_chunk(const WorkItem &w, int c)
-{
-    return w.j0 + (int64_t)c * 64 == w.i0;
-}
-
 // 64 steps of one source chunk (sources travel around the wave as in
-// sym_chunk) against the lane's R targets, FP64.  own: see own_chunk.  wx, wy, wz:
-// this axis' separations may exceed half the box (ewald_item) and are wrapped to
-// the nearest image.  A step whose pairs all lie beyond r_c skips the polynomials,
+// sym_chunk) against the lane's R targets, FP64.  wx, wy, wz: this axis'
+// separations may exceed half the box (ewald_item) and are wrapped to the
+// nearest image.  A step whose pairs all lie beyond r_c skips the polynomials,
 // one whose pairs all lie within it the second square root.  The polynomials'
 // constants are read from LDS at the start of every step, every lane the
 // same word: kept in registers they take half the waves, and scalar loads in
@@ -1997,9 +1990,9 @@ __device__ __forceinline__ bool own_chunk(const WorkItem &w, int c)
 // the math library's erf and exp (about 180 issue slots per pair; 76 now, counted)
 // a 32^3 evaluation took 2.95 ms.
 template <int R, bool REACT, bool PHI>
-__device__ __forceinline__ void ewald_chunk(bool own, bool wx, bool wy, bool wz, double sx,
-                                            double sy, double sz, double sm, double &qx,
-                                            double &qy, double &qz, double &qp,
+__device__ __forceinline__ void ewald_chunk(bool wx, bool wy, bool wz, double sx, double sy,
+                                            double sz, double sm, double &qx, double &qy,
+                                            double &qz, double &qp,
                                             const double (&xi)[R], const double (&yi)[R],
                                             const double (&zi)[R], const double (&mi)[R],
                                             double eps2, const EwaldReal &E, const double *spoly,
@@ -2088,9 +2081,9 @@ __device__ __forceinline__ void ewald_chunk(bool own, bool wx, bool wy, bool wz,
             ay[r] = fma(wt, dy[r], ay[r]);
             az[r] = fma(wt, dz[r], az[r]);
             if constexpr (PHI) {
-                // a particle's own smooth part is left to the self term
-                const double soft = nz || eps2 > 0.0 ? psi[r] : 0.0;
-                psi[r] = !nz && own && k == 0 ? soft : soft - S[r];
+                if (!(eps2 > 0.0))
+                    psi[r] = nz ? psi[r] : 0.0;
+                psi[r] -= S[r];
                 ap[r] = fma(sm, psi[r], ap[r]);
             }
             if constexpr (REACT) {
@@ -2178,8 +2171,8 @@ __device__ __forceinline__ void ewald_item(const WorkItem &w, const double *__re
         const bool wx = !__all(fabs(sx - bx) <= ex), wy = !__all(fabs(sy - by) <= ey),
                    wz = !__all(fabs(sz - bz) <= ez);
         double qx = 0.0, qy = 0.0, qz = 0.0, qp = 0.0;
-        ewald_chunk<R, REACT, PHI>(own_chunk(w, c), wx, wy, wz, sx, sy, sz, sm, qx, qy, qz, qp, xi,
-                                   yi, zi, mi, eps2, E, spoly, ax, ay, az, ap);
+        ewald_chunk<R, REACT, PHI>(wx, wy, wz, sx, sy, sz, sm, qx, qy, qz, qp, xi, yi, zi, mi,
+                                   eps2, E, spoly, ax, ay, az, ap);
         if constexpr (REACT) {
             if (jv) {
                 const int64_t rs = (int64_t)w.rslice;
@@ -2189,6 +2182,19 @@ __device__ __forceinline__ void ewald_item(const WorkItem &w, const double *__re
                 if constexpr (PHI)
                     part_phi[rs * N + j] = qp;
             }
+        }
+    }
+    if constexpr (PHI && !REACT) {
+        // a piece of a diagonal: its targets' own pairs took the limit of Phi / r off,
+        // which is the self term's
+        if (w.i0 >= w.j0 && w.i0 < w.j1) {
+            double own = spoly[2 * kWindowDegree + 2];
+#pragma unroll
+            for (int i = kWindowDegree; i >= 0; --i)
+                own += spoly[kWindowDegree + 1 + i];
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                ap[r] = fma(mi[r], own, ap[r]);
         }
     }
     const int64_t slot = (int64_t)w.slice;
@@ -2312,6 +2318,13 @@ __device__ __forceinline__ float ewald_fx_weight(const EwaldFxRegs &C, float phi
     return select_value(nz, fmaf(-P, ri * (ri * ri), rs * (rs * rs)), 0.0f);
 }
 
+// Whether source chunk c of an item holds its targets (a piece of a diagonal part):
+// each lane then meets its own particle in the chunk's first step.
+__device__ __forceinline__ bool own_chunk(const WorkItem &w, int c)
+{
+    return w.j0 + (int64_t)c * 64 == w.i0;
+}
+
 template <int R, bool REACT, bool PHI>
 __device__ __forceinline__ void ewald_chunk_fx(bool own, uint32_t sx, uint32_t sy, uint32_t sz,
                                                float sm, float &qx, float &qy, float &qz,
@@ -2371,7 +2384,7 @@ __device__ __forceinline__ void ewald_chunk_fx(bool own, uint32_t sx, uint32_t s
             for (int q = 0; q < R; ++q) {
                 const int b = u * R + q;
                 float psi = 0.0f;
-                const float phi0 = own && k + u == 0 ? E.phi_self : E.phi_same;
+                const float phi0 = !REACT && own && k + u == 0 ? E.phi_self : E.phi_same;
                 const float w = ewald_fx_weight<PHI>(C, phi0, r2[b], rs[b], ri[b], r[b], g[b], t[b],
                                                      psi);
                 const float wt = su[u] * w;
